@@ -135,9 +135,10 @@ int dwt2_forward(const void *src, const dwt2_desc *src_d, void *coef, const dwt2
  * reverse of dwt2_forward: per level, the lifting steps undone in reverse
  * order with negated coefficients (Sec. 2 and 3 define the forward steps; the
  * paper does not spell out the inverse). Arguments as for dwt2_forward. When
- * dst holds 32 MiB to 256 MiB, the finest level writes it with non-temporal
- * stores (the values are the same; the lines are not kept in the GPU
- * caches). */
+ * dst holds 32 MiB or more (one launch per level: up to 256 MiB), the finest
+ * level writes it with non-temporal stores, as the fused head of the forward
+ * does the bands of a pyramid of more than 256 MiB (the values are the same;
+ * the lines are not kept in the GPU caches). */
 int dwt2_inverse(const void *coef, const dwt2_desc *coef_d, void *dst, const dwt2_desc *dst_d,
                  dwt2_wavelet wavelet, int32_t levels, dwt2_boundary boundary,
                  dwt2_scheme scheme, void *workspace, size_t workspace_bytes,

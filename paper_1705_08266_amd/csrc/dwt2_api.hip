@@ -162,14 +162,20 @@ int pick_tile(int width, int height, int wavelet, int storage) {
 }
 
 // Sizes of reconstructed image (bytes) that dwt2_inverse writes with
-// non-temporal stores. Nothing in the transform reads its output again, and
-// streaming it keeps the 256 MiB Infinity Cache for the bands the inverse
-// reads; that measured faster from 32 MiB up to the cache's size. Smaller
-// images stay cached for whatever consumes them next; beyond the cache's size
-// there is nothing left to protect, and cached stores measured as fast or
-// faster.
+// non-temporal stores: nothing in the transform reads its output again, and
+// streaming it keeps the Infinity Cache for the bands the inverse reads.
+// Smaller images stay cached for whatever consumes them next. The one-level
+// kernels, whose row pieces share lines with their neighbours', stream only up
+// to the cache's size: beyond it there is nothing left to protect, and lines
+// that go out in two parts cost more than they save (16384^2 FP16: 636 -> 655
+// us per forward and inverse). The fused head writes whole lines and gains at
+// every size from 32 MiB on (16384^2 inverse: FP32 445 -> 401 us, FP16 229 ->
+// 212; 4096^2 FP32 32.9 -> 32.0).
+// The forward's bands are streamed, by the head, where the pyramid exceeds the
+// cache (16384^2: FP32 426 -> 399 us, FP16 229 -> 225); a smaller one stays
+// cached for its reader, often an inverse.
+constexpr int64_t kCacheBytes = (int64_t)256 << 20;   // Infinity Cache
 constexpr int64_t kStreamOutMinBytes = (int64_t)32 << 20;
-constexpr int64_t kStreamOutMaxBytes = (int64_t)256 << 20;
 
 const FwdTable &fwd_table(int dt) {
     return dt == DWT2_F32 ? kFwdF32 : dt == DWT2_F16 ? kFwdF16 : kFwdBF16;
@@ -301,6 +307,79 @@ TailPlan plan_inv_tail(int F, int wavelet, int nqx_first, int nqy_first) {
     // earlier cap of 28 quads at the finest level).
     t.B = tail_block(B, nqx_first, nqy_first);
     return t;
+}
+
+// Rows of level j+1 that a strip of a fused head owns (dwt2_head.hpp), for the
+// images (pairs of levels) of one launch. A sweep runs `halo` row pairs more
+// than it owns, so tall segments waste less; but the strips have to fill the
+// compute units, and evenly: once the memory is busy every CU gets an equal
+// share of it, so a CU with one workgroup more than the others ends that much
+// later (4096^2 FP32 forward: 31.6 us with 237 workgroups on 256 CUs, 40.8
+// with 270). So for c = 1..4 workgroups per CU the smallest segment whose grid
+// has at most c per CU is weighed, at the time its row pairs take: measured
+// 0.97, 1.8, 2.85, 3.5 us each with c = 1, 2, 3, 4 workgroups on a CU in FP32,
+// 0.83, 1.23, 1.75, 2.3 with 16-bit storage, whatever the image. Forward, us
+// with c = 1, 2, 3, 4: FP32 2048^2 12.8, 14.6 and 7680x4320 56.1, 60.0, 62.5,
+// 63.3; 16-bit 2048^2 12.5, 13.4, 4096^2 27.7, 25.1, 27.7 and 7680x4320 47.5,
+// 40.2, 39.7, 44.3. With eight or more workgroups per CU the grid evens out by
+// itself, and short segments keep the rows in flight together: 16384^2 FP32
+// forward 426 us with 9 rows (12: 436, 36: 450), inverse 445 with 15 (9: 453),
+// 16-bit 229 with 18 (9: 253).
+struct HeadShape {
+    int nqx, nqy;   // level j+1 quads
+};
+int64_t head_tasks(const HeadShape *im, int n, int seg) {
+    int64_t t = 0;
+    for (int i = 0; i < n; ++i)
+        t += (int64_t)((im[i].nqx + kHeadOwn - 1) / kHeadOwn) * ((im[i].nqy + seg - 1) / seg);
+    return t;
+}
+int head_segment(const HeadShape *im, int n, int wavelet, bool wide, bool inverse) {
+    static const double kPairTime[2][4] = {{0.83, 1.23, 1.75, 2.3}, {0.97, 1.8, 2.85, 3.5}};
+    const int64_t cus = device_cus();
+    const int many = !wide ? 18 : inverse ? 15 : 9;
+    if (head_tasks(im, n, many) >= 8 * kHeadWaves * cus) return many;
+    const int halo = wavelet == DWT2_CDF97 ? 6 : 4, D = kHeadDepth;
+    int tallest = 1;
+    for (int i = 0; i < n; ++i) tallest = std::max(tallest, im[i].nqy);
+    double best = 0;
+    int seg = tallest;
+    for (int c = 1; c <= 4; ++c) {
+        int lo = 1, hi = tallest;   // smallest segment with at most c workgroups per CU
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            if (head_tasks(im, n, mid) <= c * kHeadWaves * cus) hi = mid; else lo = mid + 1;
+        }
+        const int pairs = (lo + halo + D - 1) / D * D;   // whole groups of D
+        const double cost = pairs * kPairTime[wide][c - 1];
+        if (best == 0 || cost < best) {
+            best = cost;
+            seg = std::min(pairs - halo, tallest);
+        }
+    }
+    return seg;
+}
+
+// Strips and segments of one image's head; its number of tasks.
+// A head's accesses need word alignment only, also the 8- and 16-byte ones.
+void head_alignment(FwdHead &hd, int dt) {
+    hd.l1.vec_in = aligned(hd.l1.in, hd.l1.in_pitch, dt, dt == DWT2_F32 ? 1 : 2);
+}
+void head_alignment(InvHead &hd, int dt) {
+    hd.l1.vec_out = aligned(hd.l1.out, hd.l1.out_pitch, dt, dt == DWT2_F32 ? 1 : 2);
+}
+// full_dt: type of level j's input (forward) or output (inverse).
+template <typename H>
+int head_grid(H &hd, int seg, int full_dt) {
+    head_alignment(hd, full_dt);
+    hd.strips = (hd.l2.nqx + kHeadOwn - 1) / kHeadOwn;
+    hd.seg = seg;
+    return hd.strips * ((hd.l2.nqy + seg - 1) / seg);
+}
+template <typename H>
+int head_grid_one(H &hd, int wavelet, int dt, bool inverse) {
+    const HeadShape im{hd.l2.nqx, hd.l2.nqy};
+    return head_grid(hd, head_segment(&im, 1, wavelet, dt == DWT2_F32, inverse), dt);
 }
 
 // Size class of a level whose input is width x height pixels.
@@ -498,8 +577,12 @@ bool batch_images_conflict(const dwt2_image *images, int n, int dtype, int level
 // header, one PlanLaunch per launch, then per launch the tile -> image map,
 // each image's first tile and the images' level parameters. Offsets are from
 // the start of the plan; sections are 256-byte aligned.
+// A head launch's tile map counts blocks of level 2 quads, 58 x 18 (forward) or
+// 58 x 22 (inverse). Its kernels run strips (dwt2_head.hpp) instead: a section
+// after the parameters holds their number (in a 16-byte field), each image's
+// first one, and a map from strip to image.
 constexpr uint32_t kPlanMagic = 0x42545744u;   // "DWTB"
-constexpr int32_t kPlanVersion = 2;
+constexpr int32_t kPlanVersion = 3;
 
 struct PlanHeader {
     uint32_t magic;
@@ -522,6 +605,14 @@ const PlanLaunch *plan_launches(const PlanHeader *h) {
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// The strip section of a head launch.
+constexpr int kPlanBlockX = 58, kPlanFwdBlockY = 18, kPlanInvBlockY = 22;
+size_t head_param_size(int inverse) { return inverse ? sizeof(InvHead) : sizeof(FwdHead); }
+size_t off_strips(const PlanLaunch &l, int inverse) {
+    return align256(l.off_params + head_param_size(inverse) * (size_t)l.images);
+}
+size_t strips_bytes(size_t images, size_t strips) { return 16 + 4 * images + 4 * strips; }
 
 const FwdHeadPlanTable &fwd_head_plan_table(int dt) {
     return dt == DWT2_F32 ? kFwdHeadPlanF32 : dt == DWT2_F16 ? kFwdHeadPlanF16 : kFwdHeadPlanBF16;
@@ -552,7 +643,7 @@ int check_plan(const void *plan, size_t bytes, const PlanHeader **out) {
     for (int k = 0; k < h->nlaunch; ++k) {
         const PlanLaunch &l = L[k];
         const bool head = l.tile == DWT2_TILE_HEAD;
-        const size_t psize = head ? (h->inverse ? sizeof(InvHead) : sizeof(FwdHead))
+        const size_t psize = head ? head_param_size(h->inverse)
                                   : (h->inverse ? sizeof(InvParams) : sizeof(FwdParams));
         if (head ? (l.level != 1 || h->levels < 2) : (l.tile < 0 || l.tile >= kNumTiles))
             return DWT2_ERR_INVALID_ARG;
@@ -563,6 +654,13 @@ int check_plan(const void *plan, size_t bytes, const PlanHeader **out) {
             l.off_start + 4 * (uint64_t)l.images > bytes ||
             l.off_params + psize * (uint64_t)l.images > bytes)
             return DWT2_ERR_INVALID_ARG;
+        if (head) {
+            const size_t off = off_strips(l, h->inverse);
+            if (off + strips_bytes(l.images, 0) > bytes) return DWT2_ERR_INVALID_ARG;
+            int32_t n;
+            std::memcpy(&n, static_cast<const char *>(plan) + off, sizeof n);
+            if (n < 1 || off + strips_bytes(l.images, n) > bytes) return DWT2_ERR_INVALID_ARG;
+        }
     }
     *out = h;
     return DWT2_OK;
@@ -601,6 +699,7 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
         std::vector<InvParams> ip;
         std::vector<FwdHead> fh;
         std::vector<InvHead> ih;
+        std::vector<int32_t> strip_img, strip_start;   // head launches
     };
     std::vector<Group> groups;
     // one head launch over every image: levels 1 and 2, as dwt2_forward /
@@ -614,12 +713,20 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
         const int ll2_f32 = levels > 2 || dtype == DWT2_F32;
         G.l.f32_a = inverse ? ll2_f32 : dtype == DWT2_F32;
         G.l.f32_b = inverse ? dtype == DWT2_F32 : ll2_f32;
+        std::vector<HeadShape> shapes(n);
+        for (int i = 0; i < n; ++i) shapes[i] = {images[i].width / 4, images[i].height / 4};
+        // one segment height for the launch: its workgroups hold strips of
+        // several images
+        const int seg = head_segment(shapes.data(), n, wavelet, dtype == DWT2_F32, inverse);
+        if (head_tasks(shapes.data(), n, seg) > (int64_t)INT32_MAX - kHeadWaves)
+            return DWT2_ERR_INVALID_ARG;
+        const int block_y = inverse ? kPlanInvBlockY : kPlanFwdBlockY;
         for (int i = 0; i < n; ++i) {
             const dwt2_image &im = images[i];
             const int W = im.width, H = im.height;
             float *ws0 = static_cast<float *>(im.workspace);
             float *ws1 = ws0 + (size_t)(W / 2) * (H / 2);
-            int tiles;
+            int strips;
             if (inverse) {
                 const char *cb = static_cast<const char *>(im.src);
                 const int64_t cp = im.src_pitch;
@@ -633,9 +740,7 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
                                    cb + (size_t)((int64_t)(H / 2) * cp) * es,
                                    cb + (size_t)((int64_t)(H / 2) * cp + W / 2) * es, cp, dtype,
                                    im.dst, im.dst_pitch, dtype, W, H, wavelet, 0);
-                hd.tiles_x = (hd.l1.nqx + FwdHeadGeom::IOX1 - 1) / FwdHeadGeom::IOX1;
-                hd.tiles_y = (hd.l1.nqy + FwdHeadGeom::IOY1 - 1) / FwdHeadGeom::IOY1;
-                tiles = hd.tiles_x * hd.tiles_y;
+                strips = head_grid(hd, seg, dtype);
                 G.ih.push_back(hd);
             } else {
                 char *cb = static_cast<char *>(im.dst);
@@ -651,11 +756,13 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
                                    cb + (size_t)((int64_t)(H / 4) * cp) * es,
                                    cb + (size_t)((int64_t)(H / 4) * cp + W / 4) * es, cp, dtype,
                                    wavelet, 0);
-                hd.tiles_x = (hd.l2.nqx + FwdHeadGeom::FOX2 - 1) / FwdHeadGeom::FOX2;
-                hd.tiles_y = (hd.l2.nqy + FwdHeadGeom::FOY2 - 1) / FwdHeadGeom::FOY2;
-                tiles = hd.tiles_x * hd.tiles_y;
+                strips = head_grid(hd, seg, dtype);
                 G.fh.push_back(hd);
             }
+            G.strip_start.push_back((int32_t)G.strip_img.size());
+            G.strip_img.insert(G.strip_img.end(), (size_t)strips, (int32_t)i);
+            const int64_t tiles = (int64_t)((shapes[i].nqx + kPlanBlockX - 1) / kPlanBlockX) *
+                                  ((shapes[i].nqy + block_y - 1) / block_y);
             G.start.push_back((int32_t)G.img.size());
             if ((int64_t)G.img.size() + tiles > (int64_t)INT32_MAX) return DWT2_ERR_INVALID_ARG;
             G.img.insert(G.img.end(), (size_t)tiles, (int32_t)i);
@@ -742,6 +849,8 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
         G.l.off_params = off;
         off = align256(off + sizeof(InvParams) * G.ip.size() + sizeof(FwdParams) * G.fp.size() +
                        sizeof(InvHead) * G.ih.size() + sizeof(FwdHead) * G.fh.size());
+        if (!G.strip_img.empty())
+            off = align256(off + strips_bytes(G.strip_start.size(), G.strip_img.size()));
     }
     out.assign(off, 0);
     PlanHeader h{kPlanMagic, kPlanVersion, n, levels, inverse, dtype, wavelet,
@@ -758,6 +867,14 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
         if (!G.fh.empty()) std::memcpy(prm, G.fh.data(), sizeof(FwdHead) * G.fh.size());
         if (!G.ip.empty()) std::memcpy(prm, G.ip.data(), sizeof(InvParams) * G.ip.size());
         if (!G.fp.empty()) std::memcpy(prm, G.fp.data(), sizeof(FwdParams) * G.fp.size());
+        if (!G.strip_img.empty()) {
+            unsigned char *st = out.data() + off_strips(G.l, inverse);
+            const int32_t strips = (int32_t)G.strip_img.size();
+            std::memcpy(st, &strips, sizeof strips);
+            std::memcpy(st + 16, G.strip_start.data(), 4 * G.strip_start.size());
+            std::memcpy(st + 16 + 4 * G.strip_start.size(), G.strip_img.data(),
+                        4 * G.strip_img.size());
+        }
     }
     return DWT2_OK;
 }
@@ -953,12 +1070,12 @@ int dwt2_forward_ex(const void *src, const dwt2_desc *src_d, void *coef, const d
             (j == 1 ? hd.l1 : hd.l2) = fwd_params(in, in_pitch, in_dt, w, h, ll, ll_pitch, ll_dt,
                                                   hl, lh, hh, cp, T, wavelet, 0);
             if (j == 1) continue;
-            hd.tiles_x = (hd.l2.nqx + FwdHeadGeom::FOX2 - 1) / FwdHeadGeom::FOX2;
-            hd.tiles_y = (hd.l2.nqy + FwdHeadGeom::FOY2 - 1) / FwdHeadGeom::FOY2;
+            const int tasks = head_grid_one(hd, wavelet, T, false);
+            const bool stream_bands = (int64_t)W * H * (int64_t)es > kCacheBytes;
             if ((st = record(level_events, 0, s))) return st;
             const hipError_t e =
                 fwd_head_table(T)[wavelet][scheme][T == DWT2_F32][levels > 2 || T == DWT2_F32](
-                    hd, s);
+                    hd, tasks, stream_bands, s);
             if (e != hipSuccess) return hip_fail(e);
             for (int ev = 1; ev <= 3; ++ev)
                 if ((st = record(level_events, ev, s))) return st;
@@ -1061,18 +1178,16 @@ int dwt2_inverse_ex(const void *coef, const dwt2_desc *coef_d, void *dst, const 
         // the reconstructed image is the transform's last write
         const int64_t image_bytes = (int64_t)W * H * (int64_t)es;
         const bool stream_out = j == 1 && image_bytes >= kStreamOutMinBytes &&
-                                image_bytes <= kStreamOutMaxBytes;
+                                image_bytes <= kCacheBytes;
         if (head && j <= 2) {   // levels 2 and 1: one launch once both are planned
             (j == 2 ? hd.l2 : hd.l1) = inv_params(ll, ll_pitch, ll_dt, hl, lh, hh, cp, T, out,
                                                   out_pitch, out_dt, w, h, wavelet, 0);
             if (j == 2) continue;
-            hd.l1.stream_out = stream_out;
-            hd.tiles_x = (hd.l1.nqx + FwdHeadGeom::IOX1 - 1) / FwdHeadGeom::IOX1;
-            hd.tiles_y = (hd.l1.nqy + FwdHeadGeom::IOY1 - 1) / FwdHeadGeom::IOY1;
+            const int tasks = head_grid_one(hd, wavelet, T, true);
             if ((st = record(level_events, 0, s))) return st;
             const hipError_t e =
                 inv_head_table(T)[wavelet][scheme][levels > 2 || T == DWT2_F32][T == DWT2_F32](
-                    hd, s);
+                    hd, tasks, image_bytes >= kStreamOutMinBytes, s);
             if (e != hipSuccess) return hip_fail(e);
             for (int ev = 1; ev <= 3; ++ev)
                 if ((st = record(level_events, ev, s))) return st;
@@ -1151,20 +1266,24 @@ int dwt2_batch_run(const void *plan, size_t plan_bytes, const void *plan_device,
     for (int k = 0; k < h->nlaunch; ++k) {
         const PlanLaunch &l = L[k];
         hipError_t e;
-        if (l.tile == DWT2_TILE_HEAD && h->inverse) {
-            TableLaunch<InvHead> tl{reinterpret_cast<const int32_t *>(dev + l.off_img),
-                                    reinterpret_cast<const int32_t *>(dev + l.off_start),
-                                    reinterpret_cast<const InvHead *>(dev + l.off_params),
-                                    l.total};
-            e = inv_head_plan_table(h->dtype)[h->wavelet][scheme][l.f32_a][l.f32_b](
-                tl, persistent, stream);
-        } else if (l.tile == DWT2_TILE_HEAD) {
-            TableLaunch<FwdHead> tl{reinterpret_cast<const int32_t *>(dev + l.off_img),
-                                    reinterpret_cast<const int32_t *>(dev + l.off_start),
-                                    reinterpret_cast<const FwdHead *>(dev + l.off_params),
-                                    l.total};
-            e = fwd_head_plan_table(h->dtype)[h->wavelet][scheme][l.f32_a][l.f32_b](
-                tl, persistent, stream);
+        if (l.tile == DWT2_TILE_HEAD) {
+            const size_t off = off_strips(l, h->inverse);
+            int32_t strips;
+            std::memcpy(&strips, static_cast<const char *>(plan) + off, sizeof strips);
+            const int32_t *start = reinterpret_cast<const int32_t *>(dev + off + 16);
+            const int32_t *img = start + l.images;
+            const char *prm = dev + l.off_params;
+            if (h->inverse) {
+                const TableLaunch<InvHead> tl{img, start, reinterpret_cast<const InvHead *>(prm),
+                                              strips};
+                e = inv_head_plan_table(h->dtype)[h->wavelet][scheme][l.f32_a][l.f32_b](
+                    tl, persistent, stream);
+            } else {
+                const TableLaunch<FwdHead> tl{img, start, reinterpret_cast<const FwdHead *>(prm),
+                                              strips};
+                e = fwd_head_plan_table(h->dtype)[h->wavelet][scheme][l.f32_a][l.f32_b](
+                    tl, persistent, stream);
+            }
         } else if (h->inverse) {
             TableLaunch<InvParams> tl{reinterpret_cast<const int32_t *>(dev + l.off_img),
                                       reinterpret_cast<const int32_t *>(dev + l.off_start),
@@ -1347,13 +1466,14 @@ int head_batch(const dwt2_level_job *jobs, int32_t n, int32_t wavelet, int32_t s
     for (int g = 0; g < n && st == DWT2_OK; ++g) {   // one group per distinct key
         if (done[g]) continue;
         const HeadKey key = keys[g];
+        const int full_dt = jobs[2 * g].full_dtype;   // FP32 or the band type, by the key
         typename std::conditional<INV, InvHeadBatch, FwdHeadBatch>::type b;
+        HeadShape shapes[kHeadBatchMax];
         b.n = 0;
         b.tile_start[0] = 0;
         for (int i = g; i <= n && st == DWT2_OK; ++i) {
             if (i < n && !done[i] && keys[i] == key) {
                 const dwt2_level_job &f = jobs[2 * i], &c = jobs[2 * i + 1];
-                int tiles;
                 if constexpr (INV) {
                     InvHead &hd = b.h[b.n];
                     hd.l2 = inv_params(c.ll, c.ll_pitch, c.ll_dtype, c.hl, c.lh, c.hh,
@@ -1362,9 +1482,6 @@ int head_batch(const dwt2_level_job *jobs, int32_t n, int32_t wavelet, int32_t s
                     hd.l1 = inv_params(f.ll, f.ll_pitch, f.ll_dtype, f.hl, f.lh, f.hh,
                                        f.band_pitch, f.band_dtype, f.full, f.full_pitch,
                                        f.full_dtype, f.width, f.height, wavelet, 0);
-                    hd.tiles_x = (hd.l1.nqx + FwdHeadGeom::IOX1 - 1) / FwdHeadGeom::IOX1;
-                    hd.tiles_y = (hd.l1.nqy + FwdHeadGeom::IOY1 - 1) / FwdHeadGeom::IOY1;
-                    tiles = hd.tiles_x * hd.tiles_y;
                 } else {
                     FwdHead &hd = b.h[b.n];
                     hd.l1 = fwd_params(f.full, f.full_pitch, f.full_dtype, f.width, f.height,
@@ -1373,19 +1490,22 @@ int head_batch(const dwt2_level_job *jobs, int32_t n, int32_t wavelet, int32_t s
                     hd.l2 = fwd_params(c.full, c.full_pitch, c.full_dtype, c.width, c.height,
                                        c.ll, c.ll_pitch, c.ll_dtype, c.hl, c.lh, c.hh,
                                        c.band_pitch, c.band_dtype, wavelet, 0);
-                    hd.tiles_x = (hd.l2.nqx + FwdHeadGeom::FOX2 - 1) / FwdHeadGeom::FOX2;
-                    hd.tiles_y = (hd.l2.nqy + FwdHeadGeom::FOY2 - 1) / FwdHeadGeom::FOY2;
-                    tiles = hd.tiles_x * hd.tiles_y;
                 }
-                if ((int64_t)b.tile_start[b.n] + tiles > (int64_t)INT32_MAX) {
-                    st = DWT2_ERR_INVALID_ARG;
-                    break;
-                }
-                b.tile_start[b.n + 1] = b.tile_start[b.n] + tiles;
+                shapes[b.n] = {c.width / 2, c.height / 2};
                 ++b.n;
                 done[i] = true;
             }
             if (b.n > 0 && (b.n == kHeadBatchMax || i == n)) {
+                // one segment height for the launch: its workgroups hold strips of
+                // several images
+                const int seg =
+                    head_segment(shapes, b.n, wavelet, key.band_dt == DWT2_F32, INV);
+                if (head_tasks(shapes, b.n, seg) > (int64_t)INT32_MAX - kHeadWaves) {
+                    st = DWT2_ERR_INVALID_ARG;
+                    break;
+                }
+                for (int k = 0; k < b.n; ++k)
+                    b.tile_start[k + 1] = b.tile_start[k] + head_grid(b.h[k], seg, full_dt);
                 hipError_t e;
                 if constexpr (INV)
                     e = inv_head_batch_table(key.band_dt)[wavelet][scheme][key.a_f32][key.b_f32](

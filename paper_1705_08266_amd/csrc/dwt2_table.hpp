@@ -271,22 +271,29 @@ constexpr InvTailTable make_inv_tail_table() {
 // is FP32][level j+1's low-low output is FP32]; inverse [wavelet][scheme]
 // [level j+1's low-low input is FP32][level j's output is FP32]. The detail
 // bands are in the storage type; the band between the two levels is FP32 in
-// LDS. One configuration: 12 wavefronts of 4 quad rows.
-constexpr int kHeadRows = 4, kHeadWaves = 12;
-using FwdHeadGeom = HeadGeom<kHeadRows, kHeadWaves>;
-using FwdHeadLauncher = hipError_t (*)(const FwdHead &, hipStream_t);
-using InvHeadLauncher = hipError_t (*)(const InvHead &, hipStream_t);
+// registers. `tasks`: strips times segments; `stream`: the bands (forward) or
+// the pixels (inverse) are stored past the caches.
+using FwdHeadLauncher = hipError_t (*)(const FwdHead &, int tasks, bool stream, hipStream_t);
+using InvHeadLauncher = hipError_t (*)(const InvHead &, int tasks, bool stream, hipStream_t);
+
+inline int head_blocks(int tasks) { return (tasks + kHeadWaves - 1) / kHeadWaves; }
 
 template <int WV, int SCH, typename TIN, typename TLL, typename T>
-hipError_t launch_fwd_head(const FwdHead &h, hipStream_t s) {
-    hipLaunchKernelGGL((fwd_head_kernel<WV, SCH, kHeadRows, kHeadWaves, TIN, TLL, T>),
-                       dim3(h.tiles_x * h.tiles_y), dim3(64 * kHeadWaves), 0, s, h);
+hipError_t launch_fwd_head(const FwdHead &h, int tasks, bool stream, hipStream_t s) {
+    const dim3 grid(head_blocks(tasks)), block(64 * kHeadWaves);
+    if (stream)
+        hipLaunchKernelGGL((fwd_head_kernel<WV, SCH, TIN, TLL, T, true>), grid, block, 0, s, h, tasks);
+    else
+        hipLaunchKernelGGL((fwd_head_kernel<WV, SCH, TIN, TLL, T, false>), grid, block, 0, s, h, tasks);
     return hipGetLastError();
 }
 template <int WV, int SCH, typename TLL, typename T, typename TOUT>
-hipError_t launch_inv_head(const InvHead &h, hipStream_t s) {
-    hipLaunchKernelGGL((inv_head_kernel<WV, SCH, kHeadRows, kHeadWaves, TLL, T, TOUT>),
-                       dim3(h.tiles_x * h.tiles_y), dim3(64 * kHeadWaves), 0, s, h);
+hipError_t launch_inv_head(const InvHead &h, int tasks, bool stream, hipStream_t s) {
+    const dim3 grid(head_blocks(tasks)), block(64 * kHeadWaves);
+    if (stream)
+        hipLaunchKernelGGL((inv_head_kernel<WV, SCH, TLL, T, TOUT, true>), grid, block, 0, s, h, tasks);
+    else
+        hipLaunchKernelGGL((inv_head_kernel<WV, SCH, TLL, T, TOUT, false>), grid, block, 0, s, h, tasks);
     return hipGetLastError();
 }
 
@@ -322,8 +329,8 @@ using InvHeadTableLauncher = hipError_t (*)(const TableLaunch<InvHead> &, bool, 
 
 template <int WV, int SCH, typename TIN, typename TLL, typename T>
 hipError_t launch_fwd_head_table(const TableLaunch<FwdHead> &tl, bool persistent, hipStream_t s) {
-    const auto k = fwd_head_table_kernel<WV, SCH, kHeadRows, kHeadWaves, TIN, TLL, T>;
-    int grid = tl.total;
+    const auto k = fwd_head_table_kernel<WV, SCH, TIN, TLL, T>;
+    int grid = head_blocks(tl.total);
     if (persistent) {
         static const int resident = resident_blocks((const void *)k, 64 * kHeadWaves);
         grid = grid < resident ? grid : resident;
@@ -334,8 +341,8 @@ hipError_t launch_fwd_head_table(const TableLaunch<FwdHead> &tl, bool persistent
 }
 template <int WV, int SCH, typename TLL, typename T, typename TOUT>
 hipError_t launch_inv_head_table(const TableLaunch<InvHead> &tl, bool persistent, hipStream_t s) {
-    const auto k = inv_head_table_kernel<WV, SCH, kHeadRows, kHeadWaves, TLL, T, TOUT>;
-    int grid = tl.total;
+    const auto k = inv_head_table_kernel<WV, SCH, TLL, T, TOUT>;
+    int grid = head_blocks(tl.total);
     if (persistent) {
         static const int resident = resident_blocks((const void *)k, 64 * kHeadWaves);
         grid = grid < resident ? grid : resident;
@@ -378,17 +385,17 @@ using InvHeadBatchLauncher = hipError_t (*)(const InvHeadBatch &, hipStream_t);
 
 template <int WV, int SCH, typename TIN, typename TLL, typename T>
 hipError_t launch_fwd_head_batch(const FwdHeadBatch &b, hipStream_t s) {
-    const int grid = b.tile_start[b.n];
+    const int grid = head_blocks(b.tile_start[b.n]);
     if (grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL((fwd_head_batch_kernel<WV, SCH, kHeadRows, kHeadWaves, TIN, TLL, T>),
+    hipLaunchKernelGGL((fwd_head_batch_kernel<WV, SCH, TIN, TLL, T>),
                        dim3(grid), dim3(64 * kHeadWaves), 0, s, b);
     return hipGetLastError();
 }
 template <int WV, int SCH, typename TLL, typename T, typename TOUT>
 hipError_t launch_inv_head_batch(const InvHeadBatch &b, hipStream_t s) {
-    const int grid = b.tile_start[b.n];
+    const int grid = head_blocks(b.tile_start[b.n]);
     if (grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL((inv_head_batch_kernel<WV, SCH, kHeadRows, kHeadWaves, TLL, T, TOUT>),
+    hipLaunchKernelGGL((inv_head_batch_kernel<WV, SCH, TLL, T, TOUT>),
                        dim3(grid), dim3(64 * kHeadWaves), 0, s, b);
     return hipGetLastError();
 }
