@@ -19,7 +19,8 @@ is rejected at arrival.
 
 ``Scheduler`` is the host-side policy (no GPU, testable with a simulated
 clock); ``Server`` allocates buffers with PyTorch, builds the per-level job
-descriptors once at admission and drives the library on one HIP stream.
+descriptors once, when an admitted request's first step is due, and drives the
+library on one HIP stream.
 Latency is measured from the request's arrival to the GPU timestamp of the
 iteration that finished it.
 """
@@ -31,10 +32,18 @@ import dataclasses
 import fractions
 import gc
 import math
+import struct
 import time
 
 from . import _lib
 from . import _scheme, _stream_ptr, _wavelet, load
+
+# Level-input pixels after which an idle device is given what has been prepared
+# so far. Preparing a request (three allocations, its job records) takes the host
+# about 11 us, so 24 requests that arrive at once leave the device idle for
+# 0.37 ms if all are prepared first; 64 Mpx keep it busy for about 60 us, longer
+# than the host needs to prepare and launch the next as many.
+_FEED_PIXELS = 64 << 20
 
 _STORAGE_BYTES = {_lib.F32: 4, _lib.F16: 2, _lib.BF16: 2}
 
@@ -227,6 +236,12 @@ def _job(full, ll, hl, lh, hh, width, height, dtcode):
     return j
 
 
+# One dwt2_level_job as a packed record (native layout, padded to its size):
+# packing a job is one call instead of a dozen field assignments.
+_JOB = struct.Struct("@PqiPqiPPPqiii0P")
+assert _JOB.size == ctypes.sizeof(_lib.LevelJob)
+
+
 def ll_slots(width: int, height: int, levels: int, fuse_heads: bool = False):
     """Where each intermediate low-low band LL_k (1 <= k < levels, the output
     of level k's forward) lives: k -> (buffer 0 or 1, offset in floats).
@@ -281,26 +296,16 @@ def level_jobs(src, out, ws0, ws1, levels, inverse, fuse_heads=False):
         b, off = slots[k]
         return ws[b] + 4 * off
 
-    jobs = (_lib.LevelJob * levels)()
+    buf = bytearray(levels * _JOB.size)
     order = range(levels, 0, -1) if inverse else range(1, levels + 1)
     for k, j in enumerate(order):
         h, w = H >> (j - 1), W >> (j - 1)
         h2, w2 = h // 2, w // 2
-        job = jobs[k]
-        if j == 1:
-            job.full, job.full_pitch, job.full_dtype = img, P, dt
-        else:
-            job.full, job.full_pitch, job.full_dtype = band(j - 1), w, _lib.F32
-        if j == levels:
-            job.ll, job.ll_pitch, job.ll_dtype = pyr, P, dt
-        else:
-            job.ll, job.ll_pitch, job.ll_dtype = band(j), w2, _lib.F32
-        job.hl = pyr + e * w2
-        job.lh = pyr + e * h2 * P
-        job.hh = pyr + e * (h2 * P + w2)
-        job.band_pitch, job.band_dtype = P, dt
-        job.width, job.height = w, h
-    return jobs
+        full = (img, P, dt) if j == 1 else (band(j - 1), w, _lib.F32)
+        ll = (pyr, P, dt) if j == levels else (band(j), w2, _lib.F32)
+        _JOB.pack_into(buf, k * _JOB.size, *full, *ll, pyr + e * w2, pyr + e * h2 * P,
+                       pyr + e * (h2 * P + w2), P, dt, w, h)
+    return (_lib.LevelJob * levels).from_buffer(buf)
 
 
 @dataclasses.dataclass
@@ -373,23 +378,20 @@ class Server:
         ws0 = torch.empty(n0, dtype=torch.float32, device=src.device)
         ws1 = torch.empty(n1, dtype=torch.float32, device=src.device)
         jobs = level_jobs(src, out, ws0, ws1, req.levels, req.inverse, self.fuse_heads)
-        # first job (execution order) of each step
-        first, k = [], 0
+        # each step's jobs as bytes, a head pair as (finer, coarser) level
+        raw, size, steps, k = bytes(jobs), _JOB.size, [], 0
         for n in a.steps:
-            first.append(k)
+            part = raw[k * size:(k + n) * size]
+            steps.append(part[size:] + part[:size] if n == 2 and req.inverse else part)
             k += n
-        a.payload = {"out": out, "ws": (ws0, ws1), "jobs": jobs, "first": first}
+        a.payload = {"out": out, "ws": (ws0, ws1), "steps": steps}
 
     def _enqueue(self, advanced, stream):
         lib = load()
         calls = {(inv, n): [] for inv in (False, True) for n in (1, 2)}
         for a in advanced:
-            jobs, k = a.payload["jobs"], a.payload["first"][a.next_level]
-            n, inv = a.steps[a.next_level], a.req.inverse
-            if n == 1:
-                calls[(inv, 1)].append(jobs[k])
-            else:                        # a head pair as (finer, coarser) level
-                calls[(inv, 2)] += (jobs[k + 1], jobs[k]) if inv else (jobs[k], jobs[k + 1])
+            k = a.next_level
+            calls[(a.req.inverse, a.steps[k])].append(a.payload["steps"][k])
         fns = {(False, 1): ("dwt2_forward_level_batch", True),
                (True, 1): ("dwt2_inverse_level_batch", True),
                (False, 2): ("dwt2_forward_head_batch", False),
@@ -398,8 +400,8 @@ class Server:
             if not jobs:
                 continue
             name, tiles = fns[key]
-            arr = (_lib.LevelJob * len(jobs))(*jobs)
-            n = len(jobs) // key[1]
+            n = len(jobs)
+            arr = (_lib.LevelJob * (n * key[1])).from_buffer_copy(b"".join(jobs))
             args = (arr, n, self.wavelet, self.scheme) + ((self.class_tiles,) if tiles else ())
             _lib.check(getattr(lib, name)(*args, stream), name)
             self.launch_calls += 1
@@ -449,13 +451,23 @@ class Server:
                     if not self.sched.offer(r):            # can never fit the budget
                         results.append(Result(r.rid, r.arrival_s, float("nan"), None,
                                               rejected=True))
-                for a in self.sched.admit(now):
-                    self._allocate(a, inputs, torch)
+                self.sched.admit(now)
                 advanced = self.sched.iteration()
                 if advanced:
                     ev0 = torch.cuda.Event(enable_timing=True)
                     ev0.record(stream)
-                    self._enqueue(advanced, sptr)
+                    # buffers and jobs of the requests that start; while nothing is
+                    # queued on the device, it gets them in portions
+                    first, px = 0, 0
+                    for i, a in enumerate(advanced):
+                        if a.payload is None:
+                            self._allocate(a, inputs, torch)
+                        px += a.step_px[a.next_level]
+                        if px >= _FEED_PIXELS and not inflight:
+                            self._enqueue(advanced[first:i + 1], sptr)
+                            first, px = i + 1, 0
+                    if first < len(advanced):
+                        self._enqueue(advanced[first:], sptr)
                     done = self.sched.finish_iteration(advanced)
                     ev = torch.cuda.Event(enable_timing=True)
                     ev.record(stream)
