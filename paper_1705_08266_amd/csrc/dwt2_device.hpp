@@ -88,15 +88,10 @@ template <> __device__ __forceinline__ __half from_float<__half>(float v) {
     asm volatile("" : "+v"(v));
     return __float2half_rn(v);
 }
+// A NaN stays a quiet NaN with its sign.
 template <> __device__ __forceinline__ bf16_t from_float<bf16_t>(float v) {
-    uint32_t u = __float_as_uint(v);
     bf16_t r;
-    if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x007fffffu)) {
-        r.bits = 0x7fc0;                       // quiet NaN
-    } else {
-        u += 0x7fffu + ((u >> 16) & 1u);       // round half to even
-        r.bits = (uint16_t)(u >> 16);
-    }
+    r.bits = __builtin_bit_cast(uint16_t, (__bf16)v);
     return r;
 }
 
@@ -104,6 +99,27 @@ template <typename T> __device__ __forceinline__ uint32_t bits_of(T v);
 template <> __device__ __forceinline__ uint32_t bits_of<float>(float v) { return __float_as_uint(v); }
 template <> __device__ __forceinline__ uint32_t bits_of<__half>(__half v) { return (uint32_t)__half_as_ushort(v); }
 template <> __device__ __forceinline__ uint32_t bits_of<bf16_t>(bf16_t v) { return v.bits; }
+
+// Two values as one word of 2-byte elements (lo in the low half), by the
+// hardware's packed conversion: the same bits as from_float for every input
+// (all 2^32 compared), in one instruction where two conversions and their
+// packing take three (FP16) and rounding in integers with its NaN test took
+// about a dozen (BF16). The fused heads are bound by the instructions they
+// issue at these sizes: 2048^2 BF16 forward 15.4 -> 13.3 us, 4096^2 27.4 -> 24.9.
+template <typename T> __device__ __forceinline__ uint32_t pack2(float lo, float hi);
+template <> __device__ __forceinline__ uint32_t pack2<__half>(float lo, float hi) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    asm volatile("" : "+v"(lo), "+v"(hi));   // FP32 values first, as in from_float
+    const f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
+}
+template <> __device__ __forceinline__ uint32_t pack2<bf16_t>(float lo, float hi) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
 
 // ---- vector row access through buffer resources ---------------------------------
 // A row of a 2-D buffer is described by a wave-uniform buffer resource (base
@@ -221,8 +237,7 @@ __device__ __forceinline__ void store_vec(rsrc_t r, uint32_t off, const float (&
         } else {
 #pragma unroll
             for (int e = 0; e < N; e += 2)
-                w[e / 2] = bits_of<T>(from_float<T>(in[e])) |
-                           (bits_of<T>(from_float<T>(in[e + 1])) << 16);
+                w[e / 2] = pack2<T>(in[e], in[e + 1]);
         }
         buf_store_words<BYTES / 4, POLICY>(r, off, w);
     }

@@ -156,8 +156,7 @@ struct RowsOf {
             w[0] = bits_of<T>(from_float<T>(v[0]));
         } else {
 #pragma unroll
-            for (int i = 0; i < N; i += 2)
-                w[i / 2] = bits_of<T>(from_float<T>(v[i])) | (bits_of<T>(from_float<T>(v[i + 1])) << 16);
+            for (int i = 0; i < N; i += 2) w[i / 2] = pack2<T>(v[i], v[i + 1]);
         }
         if constexpr (HALF && N == 1) {
             __builtin_amdgcn_raw_buffer_store_b16((unsigned short)w[0], r, (int)off,
