@@ -360,8 +360,46 @@ int head_segment(const HeadShape *im, int n, int wavelet, bool wide, bool invers
     return seg;
 }
 
-// Strips and segments of one image's head; its number of tasks.
-// A head's accesses need word alignment only, also the 8- and 16-byte ones.
+// Windows (dwt2_head_tile.hpp) of an image, counted in level j+1 quads.
+int64_t head_windows(const HeadShape &im, bool inverse) {
+    constexpr int X = HeadWindow::FOX2, FY = HeadWindow::FOY2, IY = HeadWindow::IOY1 / 2;
+    static_assert(2 * X == HeadWindow::IOX1, "windows of either direction are as wide");
+    const int y = inverse ? IY : FY;
+    return (int64_t)((im.nqx + X - 1) / X) * ((im.nqy + y - 1) / y);
+}
+// Whether a head launch runs by windows instead of strips. A launch of few
+// windows has them all resident, two to a CU, and ends after about one
+// window's time; one of many pays their halo and their phases in full, and
+// strips are faster. Measured, us by windows and by strips (bands in the caches
+// where they fit; from memory), the counts on 256 CUs:
+//   9/7 forward FP32: 75 windows 8.6, 9.2 (8.8, 9.3); 504: 13.8, 16.0 (17.9, 19.7);
+//     602: 17.7, 16.3 (23.7, 21.4); 261, in between: 12.2, 11.9 (14.5, 12.8)
+//   9/7 forward 16-bit: 240: 9.7, 12.2 (11.4, 12.3); 774: 18.8, 19.7 (21.5, 21.0);
+//     1368: 26.4, 25.2 (32.5, 28.3)
+//   9/7 inverse FP32: 60: 8.6, 9.6 (8.9, 9.6); 490: 14.7, 17.3 (20.7, 21.7);
+//     630: 20.7, 20.3 (29.3, 27.3)
+//   9/7 inverse 16-bit: 216: 9.6, 12.8 (11.3, 13.1); 630: 18.9, 20.6 (23.2, 21.5);
+//     846: 23.1, 24.0 (29.8, 24.9)
+// The 5/3 strips carry half the stages and less halo, and are faster at every
+// size (forward: see kFwdByWindows; inverse FP32 72: 7.5, 6.2 (8.4, 6.5), 490: 13.8,
+// 13.6 (20.7, 19.7)) but one: 16-bit inverse, 72: 7.4, 6.3 (7.7, 6.3); 117: 7.6,
+// 8.0 (7.9, 8.0); 216: 8.3, 10.1 (10.1, 10.6); 360: 11.9, 11.0 (14.8, 12.2).
+bool head_by_windows(const HeadShape *im, int n, int wavelet, bool wide, bool inverse) {
+    const int64_t cus = device_cus();
+    int64_t w = 0;
+    for (int i = 0; i < n; ++i) w += head_windows(im[i], inverse);
+    if (wavelet == DWT2_CDF97) return w <= cus * (wide ? 2 : inverse ? 3 : 4);
+    return inverse && !wide && 8 * w > 3 * cus && w <= cus;
+}
+// The rows per segment of a head launch, or 0 where it runs by windows.
+int head_layout(const HeadShape *im, int n, int wavelet, bool wide, bool inverse) {
+    return head_by_windows(im, n, wavelet, wide, inverse)
+               ? 0 : head_segment(im, n, wavelet, wide, inverse);
+}
+
+// Layout of one image's head in a launch, by windows (seg 0) or strips; its
+// number of tasks. A head's accesses need word alignment only, also the 8- and
+// 16-byte ones.
 void head_alignment(FwdHead &hd, int dt) {
     hd.l1.vec_in = aligned(hd.l1.in, hd.l1.in_pitch, dt, dt == DWT2_F32 ? 1 : 2);
 }
@@ -371,15 +409,17 @@ void head_alignment(InvHead &hd, int dt) {
 // full_dt: type of level j's input (forward) or output (inverse).
 template <typename H>
 int head_grid(H &hd, int seg, int full_dt) {
+    constexpr int X = HeadWindow::FOX2;
     head_alignment(hd, full_dt);
-    hd.strips = (hd.l2.nqx + kHeadOwn - 1) / kHeadOwn;
     hd.seg = seg;
-    return hd.strips * ((hd.l2.nqy + seg - 1) / seg);
+    hd.across = seg ? (hd.l2.nqx + kHeadOwn - 1) / kHeadOwn : (hd.l2.nqx + X - 1) / X;
+    const HeadShape im{hd.l2.nqx, hd.l2.nqy};
+    return (int)(seg ? head_tasks(&im, 1, seg) : head_windows(im, std::is_same<H, InvHead>::value));
 }
 template <typename H>
 int head_grid_one(H &hd, int wavelet, int dt, bool inverse) {
     const HeadShape im{hd.l2.nqx, hd.l2.nqy};
-    return head_grid(hd, head_segment(&im, 1, wavelet, dt == DWT2_F32, inverse), dt);
+    return head_grid(hd, head_layout(&im, 1, wavelet, dt == DWT2_F32, inverse), dt);
 }
 
 // Size class of a level whose input is width x height pixels.
@@ -577,10 +617,10 @@ bool batch_images_conflict(const dwt2_image *images, int n, int dtype, int level
 // header, one PlanLaunch per launch, then per launch the tile -> image map,
 // each image's first tile and the images' level parameters. Offsets are from
 // the start of the plan; sections are 256-byte aligned.
-// A head launch's tile map counts blocks of level 2 quads, 58 x 18 (forward) or
-// 58 x 22 (inverse). Its kernels run strips (dwt2_head.hpp) instead: a section
-// after the parameters holds their number (in a 16-byte field), each image's
-// first one, and a map from strip to image.
+// A head launch's tile map counts windows (dwt2_head_tile.hpp). Where it runs
+// strips (dwt2_head.hpp) instead, a section after the parameters holds their
+// map: their number (in a 16-byte field; 0: the launch runs windows), each
+// image's first one, and the image of each.
 constexpr uint32_t kPlanMagic = 0x42545744u;   // "DWTB"
 constexpr int32_t kPlanVersion = 3;
 
@@ -607,12 +647,13 @@ const PlanLaunch *plan_launches(const PlanHeader *h) {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // The strip section of a head launch.
-constexpr int kPlanBlockX = 58, kPlanFwdBlockY = 18, kPlanInvBlockY = 22;
 size_t head_param_size(int inverse) { return inverse ? sizeof(InvHead) : sizeof(FwdHead); }
 size_t off_strips(const PlanLaunch &l, int inverse) {
     return align256(l.off_params + head_param_size(inverse) * (size_t)l.images);
 }
-size_t strips_bytes(size_t images, size_t strips) { return 16 + 4 * images + 4 * strips; }
+size_t strips_bytes(size_t images, size_t strips) {
+    return strips ? 16 + 4 * images + 4 * strips : 16;
+}
 
 const FwdHeadPlanTable &fwd_head_plan_table(int dt) {
     return dt == DWT2_F32 ? kFwdHeadPlanF32 : dt == DWT2_F16 ? kFwdHeadPlanF16 : kFwdHeadPlanBF16;
@@ -656,10 +697,10 @@ int check_plan(const void *plan, size_t bytes, const PlanHeader **out) {
             return DWT2_ERR_INVALID_ARG;
         if (head) {
             const size_t off = off_strips(l, h->inverse);
-            if (off + strips_bytes(l.images, 0) > bytes) return DWT2_ERR_INVALID_ARG;
+            if (off + 16 > bytes) return DWT2_ERR_INVALID_ARG;
             int32_t n;
             std::memcpy(&n, static_cast<const char *>(plan) + off, sizeof n);
-            if (n < 1 || off + strips_bytes(l.images, n) > bytes) return DWT2_ERR_INVALID_ARG;
+            if (n < 0 || off + strips_bytes(l.images, n) > bytes) return DWT2_ERR_INVALID_ARG;
         }
     }
     *out = h;
@@ -715,18 +756,17 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
         G.l.f32_b = inverse ? dtype == DWT2_F32 : ll2_f32;
         std::vector<HeadShape> shapes(n);
         for (int i = 0; i < n; ++i) shapes[i] = {images[i].width / 4, images[i].height / 4};
-        // one segment height for the launch: its workgroups hold strips of
-        // several images
-        const int seg = head_segment(shapes.data(), n, wavelet, dtype == DWT2_F32, inverse);
-        if (head_tasks(shapes.data(), n, seg) > (int64_t)INT32_MAX - kHeadWaves)
+        // one layout and segment height for the launch: its workgroups hold
+        // strips of several images
+        const int seg = head_layout(shapes.data(), n, wavelet, dtype == DWT2_F32, inverse);
+        if (seg && head_tasks(shapes.data(), n, seg) > (int64_t)INT32_MAX - kHeadWaves)
             return DWT2_ERR_INVALID_ARG;
-        const int block_y = inverse ? kPlanInvBlockY : kPlanFwdBlockY;
         for (int i = 0; i < n; ++i) {
             const dwt2_image &im = images[i];
             const int W = im.width, H = im.height;
             float *ws0 = static_cast<float *>(im.workspace);
             float *ws1 = ws0 + (size_t)(W / 2) * (H / 2);
-            int strips;
+            int tasks;
             if (inverse) {
                 const char *cb = static_cast<const char *>(im.src);
                 const int64_t cp = im.src_pitch;
@@ -740,7 +780,7 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
                                    cb + (size_t)((int64_t)(H / 2) * cp) * es,
                                    cb + (size_t)((int64_t)(H / 2) * cp + W / 2) * es, cp, dtype,
                                    im.dst, im.dst_pitch, dtype, W, H, wavelet, 0);
-                strips = head_grid(hd, seg, dtype);
+                tasks = head_grid(hd, seg, dtype);
                 G.ih.push_back(hd);
             } else {
                 char *cb = static_cast<char *>(im.dst);
@@ -756,13 +796,14 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
                                    cb + (size_t)((int64_t)(H / 4) * cp) * es,
                                    cb + (size_t)((int64_t)(H / 4) * cp + W / 4) * es, cp, dtype,
                                    wavelet, 0);
-                strips = head_grid(hd, seg, dtype);
+                tasks = head_grid(hd, seg, dtype);
                 G.fh.push_back(hd);
             }
-            G.strip_start.push_back((int32_t)G.strip_img.size());
-            G.strip_img.insert(G.strip_img.end(), (size_t)strips, (int32_t)i);
-            const int64_t tiles = (int64_t)((shapes[i].nqx + kPlanBlockX - 1) / kPlanBlockX) *
-                                  ((shapes[i].nqy + block_y - 1) / block_y);
+            if (seg) {
+                G.strip_start.push_back((int32_t)G.strip_img.size());
+                G.strip_img.insert(G.strip_img.end(), (size_t)tasks, (int32_t)i);
+            }
+            const int64_t tiles = head_windows(shapes[i], inverse);
             G.start.push_back((int32_t)G.img.size());
             if ((int64_t)G.img.size() + tiles > (int64_t)INT32_MAX) return DWT2_ERR_INVALID_ARG;
             G.img.insert(G.img.end(), (size_t)tiles, (int32_t)i);
@@ -849,7 +890,7 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
         G.l.off_params = off;
         off = align256(off + sizeof(InvParams) * G.ip.size() + sizeof(FwdParams) * G.fp.size() +
                        sizeof(InvHead) * G.ih.size() + sizeof(FwdHead) * G.fh.size());
-        if (!G.strip_img.empty())
+        if (!G.ih.empty() || !G.fh.empty())
             off = align256(off + strips_bytes(G.strip_start.size(), G.strip_img.size()));
     }
     out.assign(off, 0);
@@ -1270,19 +1311,23 @@ int dwt2_batch_run(const void *plan, size_t plan_bytes, const void *plan_device,
             const size_t off = off_strips(l, h->inverse);
             int32_t strips;
             std::memcpy(&strips, static_cast<const char *>(plan) + off, sizeof strips);
-            const int32_t *start = reinterpret_cast<const int32_t *>(dev + off + 16);
-            const int32_t *img = start + l.images;
+            const bool windows = strips == 0;
+            const int32_t *start = reinterpret_cast<const int32_t *>(
+                dev + (windows ? (size_t)l.off_start : off + 16));
+            const int32_t *img = windows ? reinterpret_cast<const int32_t *>(dev + l.off_img)
+                                         : start + l.images;
+            const int32_t tasks = windows ? l.total : strips;
             const char *prm = dev + l.off_params;
             if (h->inverse) {
                 const TableLaunch<InvHead> tl{img, start, reinterpret_cast<const InvHead *>(prm),
-                                              strips};
+                                              tasks};
                 e = inv_head_plan_table(h->dtype)[h->wavelet][scheme][l.f32_a][l.f32_b](
-                    tl, persistent, stream);
+                    tl, windows, persistent, stream);
             } else {
                 const TableLaunch<FwdHead> tl{img, start, reinterpret_cast<const FwdHead *>(prm),
-                                              strips};
+                                              tasks};
                 e = fwd_head_plan_table(h->dtype)[h->wavelet][scheme][l.f32_a][l.f32_b](
-                    tl, persistent, stream);
+                    tl, windows, persistent, stream);
             }
         } else if (h->inverse) {
             TableLaunch<InvParams> tl{reinterpret_cast<const int32_t *>(dev + l.off_img),
@@ -1496,11 +1541,10 @@ int head_batch(const dwt2_level_job *jobs, int32_t n, int32_t wavelet, int32_t s
                 done[i] = true;
             }
             if (b.n > 0 && (b.n == kHeadBatchMax || i == n)) {
-                // one segment height for the launch: its workgroups hold strips of
-                // several images
-                const int seg =
-                    head_segment(shapes, b.n, wavelet, key.band_dt == DWT2_F32, INV);
-                if (head_tasks(shapes, b.n, seg) > (int64_t)INT32_MAX - kHeadWaves) {
+                // one layout and segment height for the launch: its workgroups
+                // hold strips of several images
+                const int seg = head_layout(shapes, b.n, wavelet, key.band_dt == DWT2_F32, INV);
+                if (seg && head_tasks(shapes, b.n, seg) > (int64_t)INT32_MAX - kHeadWaves) {
                     st = DWT2_ERR_INVALID_ARG;
                     break;
                 }

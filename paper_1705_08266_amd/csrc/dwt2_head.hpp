@@ -65,13 +65,14 @@ struct HeadGeom {
 struct FwdHead {
     FwdParams l1;             // level j: input and detail bands (its ll is unused)
     FwdParams l2;             // level j+1: detail bands and low-low output (its in is unused)
-    int32_t strips, seg;      // strips per row of tasks; rows of level j+1 per segment
+    int32_t across;           // strips per row of tasks, or windows per row of windows
+    int32_t seg;              // rows of level j+1 per segment; 0: windows (dwt2_head_tile.hpp)
 };
 
 struct InvHead {
     InvParams l2;             // level j+1: low-low and detail bands (its out is unused)
     InvParams l1;             // level j: detail bands and output (its ll is unused)
-    int32_t strips, seg;
+    int32_t across, seg;
 };
 
 // One strip's segment, forward: rows o..o+seg of level j+1, the window's first
@@ -309,7 +310,7 @@ __device__ __forceinline__ bool within_span(int64_t rows, int64_t pitch) {
 template <int WV, int SCH, int OWN, typename TIN, typename TLL, typename TB, bool STREAM>
 __device__ __forceinline__ void fwd_head_task(const FwdHead &hd, const int task) {
     using G = HeadGeom<WV, OWN>;
-    const int sg = task / hd.strips, st = task - sg * hd.strips;
+    const int sg = task / hd.across, st = task - sg * hd.across;
     const int wx = st * OWN - G::HALO, o = sg * hd.seg;
     const FwdParams &p1 = hd.l1, &p2 = hd.l2;
     const int64_t rows = 4 * (int64_t)(hd.seg + 8 + 2 * kHeadDepth);
@@ -341,7 +342,7 @@ __device__ __forceinline__ void fwd_head_task(const FwdHead &hd, const int task)
 template <int WV, int SCH, int OWN, typename TLL, typename TB, typename TOUT, bool STREAM>
 __device__ __forceinline__ void inv_head_task(const InvHead &hd, const int task) {
     using G = HeadGeom<WV, OWN>;
-    const int sg = task / hd.strips, st = task - sg * hd.strips;
+    const int sg = task / hd.across, st = task - sg * hd.across;
     const int wx = st * OWN - G::HALO, o = sg * hd.seg;
     const InvParams &p1 = hd.l1, &p2 = hd.l2;
     const int64_t rows = 4 * (int64_t)(hd.seg + 8 + 2 * kHeadDepth);
