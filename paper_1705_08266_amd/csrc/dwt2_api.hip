@@ -383,13 +383,14 @@ int64_t head_windows(const HeadShape &im, bool inverse) {
 // The 5/3 strips carry half the stages and less halo, and are faster at every
 // size (forward: see kFwdByWindows; inverse FP32 72: 7.5, 6.2 (8.4, 6.5), 490: 13.8,
 // 13.6 (20.7, 19.7)) but one: 16-bit inverse, 72: 7.4, 6.3 (7.7, 6.3); 117: 7.6,
-// 8.0 (7.9, 8.0); 216: 8.3, 10.1 (10.1, 10.6); 360: 11.9, 11.0 (14.8, 12.2).
+// 8.0 (7.9, 8.0); 216: 8.3, 10.1 (10.1, 10.6); 342: 10.2, 11.0; 360: 11.9, 11.0
+// (14.8, 12.2).
 bool head_by_windows(const HeadShape *im, int n, int wavelet, bool wide, bool inverse) {
     const int64_t cus = device_cus();
     int64_t w = 0;
     for (int i = 0; i < n; ++i) w += head_windows(im[i], inverse);
     if (wavelet == DWT2_CDF97) return w <= cus * (wide ? 2 : inverse ? 3 : 4);
-    return inverse && !wide && 8 * w > 3 * cus && w <= cus;
+    return inverse && !wide && 8 * w > 3 * cus && 8 * w <= 11 * cus;
 }
 // The rows per segment of a head launch, or 0 where it runs by windows.
 int head_layout(const HeadShape *im, int n, int wavelet, bool wide, bool inverse) {

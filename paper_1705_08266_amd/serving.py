@@ -36,7 +36,7 @@ import struct
 import time
 
 from . import _lib
-from . import _scheme, _stream_ptr, _wavelet, load
+from . import _dtype_code, _scheme, _stream_ptr, _wavelet, load
 
 # Level-input pixels after which an idle device is given what has been prepared
 # so far. Preparing a request (three allocations, its job records) takes the host
@@ -280,32 +280,46 @@ def level_jobs(src, out, ws0, ws1, levels, inverse, fuse_heads=False):
     head launch). Pointers are computed directly (this runs once per admitted
     request).
     """
-    from . import _dtype_code
-    H, W = src.shape
+    return (_lib.LevelJob * levels).from_buffer(
+        _packed_jobs(src, out, ws0, ws1, levels, inverse, fuse_heads))
+
+
+def _packed_jobs(src, out, ws0, ws1, levels, inverse, fuse_heads):
+    """level_jobs as packed records."""
     P = src.stride(0)
     if out.stride(0) != P or out.shape != src.shape or out.dtype != src.dtype:
         raise ValueError("src and out must share shape, dtype and row pitch")
+    h, w = src.shape
     dt = _dtype_code(src)
     e = src.element_size()
-    pyr = (src if inverse else out).data_ptr()
-    img = (out if inverse else src).data_ptr()
+    pyr, img = out.data_ptr(), src.data_ptr()
+    if inverse:
+        pyr, img = img, pyr
     ws = (ws0.data_ptr(), ws1.data_ptr())
-    slots = ll_slots(W, H, levels, fuse_heads)
+    slots = ll_slots(w, h, levels, fuse_heads)
+    size, pack, f32 = _JOB.size, _JOB.pack_into, _lib.F32
+    buf = bytearray(levels * size)
+    full = (img, P, dt)
+    for j in range(1, levels + 1):
+        h2, w2 = h >> 1, w >> 1
+        if j == levels:
+            ll = (pyr, P, dt)
+        else:
+            i, off = slots[j]                # LL_j
+            ll = (ws[i] + 4 * off, w2, f32)
+        lh = pyr + e * h2 * P
+        pack(buf, (levels - j if inverse else j - 1) * size, *full, *ll, pyr + e * w2, lh,
+             lh + e * w2, P, dt, w, h)
+        full, h, w = ll, h2, w2
+    return buf
 
-    def band(k):                     # address of LL_k
-        b, off = slots[k]
-        return ws[b] + 4 * off
 
-    buf = bytearray(levels * _JOB.size)
-    order = range(levels, 0, -1) if inverse else range(1, levels + 1)
-    for k, j in enumerate(order):
-        h, w = H >> (j - 1), W >> (j - 1)
-        h2, w2 = h // 2, w // 2
-        full = (img, P, dt) if j == 1 else (band(j - 1), w, _lib.F32)
-        ll = (pyr, P, dt) if j == levels else (band(j), w2, _lib.F32)
-        _JOB.pack_into(buf, k * _JOB.size, *full, *ll, pyr + e * w2, pyr + e * h2 * P,
-                       pyr + e * (h2 * P + w2), P, dt, w, h)
-    return (_lib.LevelJob * levels).from_buffer(buf)
+# (inverse, levels of the step) -> the call that enqueues such steps, and whether
+# it takes the size classes' tiles; in the order of their launches.
+_CALLS = {(False, 1): ("dwt2_forward_level_batch", True),
+          (False, 2): ("dwt2_forward_head_batch", False),
+          (True, 1): ("dwt2_inverse_level_batch", True),
+          (True, 2): ("dwt2_inverse_head_batch", False)}
 
 
 @dataclasses.dataclass
@@ -377,29 +391,29 @@ class Server:
         n1 = (req.width // 4) * (req.height // 4) if req.levels > 2 else 1
         ws0 = torch.empty(n0, dtype=torch.float32, device=src.device)
         ws1 = torch.empty(n1, dtype=torch.float32, device=src.device)
-        jobs = level_jobs(src, out, ws0, ws1, req.levels, req.inverse, self.fuse_heads)
+        raw = _packed_jobs(src, out, ws0, ws1, req.levels, req.inverse, self.fuse_heads)
         # each step's jobs as bytes, a head pair as (finer, coarser) level
-        raw, size, steps, k = bytes(jobs), _JOB.size, [], 0
+        size, steps, k = _JOB.size, [], 0
         for n in a.steps:
-            part = raw[k * size:(k + n) * size]
-            steps.append(part[size:] + part[:size] if n == 2 and req.inverse else part)
-            k += n
+            end = k + n * size
+            if n == 2 and req.inverse:
+                steps.append(raw[k + size:end] + raw[k:k + size])
+            else:
+                steps.append(raw[k:end])
+            k = end
         a.payload = {"out": out, "ws": (ws0, ws1), "steps": steps}
 
     def _enqueue(self, advanced, stream):
         lib = load()
-        calls = {(inv, n): [] for inv in (False, True) for n in (1, 2)}
+        calls = {}
         for a in advanced:
             k = a.next_level
-            calls[(a.req.inverse, a.steps[k])].append(a.payload["steps"][k])
-        fns = {(False, 1): ("dwt2_forward_level_batch", True),
-               (True, 1): ("dwt2_inverse_level_batch", True),
-               (False, 2): ("dwt2_forward_head_batch", False),
-               (True, 2): ("dwt2_inverse_head_batch", False)}
-        for key, jobs in calls.items():
-            if not jobs:
+            calls.setdefault((a.req.inverse, a.steps[k]), []).append(a.payload["steps"][k])
+        for key in _CALLS:
+            jobs = calls.get(key)
+            if jobs is None:
                 continue
-            name, tiles = fns[key]
+            name, tiles = _CALLS[key]
             n = len(jobs)
             arr = (_lib.LevelJob * (n * key[1])).from_buffer_copy(b"".join(jobs))
             args = (arr, n, self.wavelet, self.scheme) + ((self.class_tiles,) if tiles else ())
@@ -411,7 +425,6 @@ class Server:
         request is offered at time zero (saturation). Returns the results in
         completion order."""
         import torch
-        from . import _dtype_code
         for r in requests:
             if _dtype_code(inputs[r.rid]) != self.dtype:
                 raise ValueError(f"request {r.rid}: input dtype differs from the server's")

@@ -24,7 +24,7 @@ def _cus():
 @pytest.mark.parametrize("wavelet,dtype,inverse,eighths",
                          [("cdf97", torch.float32, False, 16), ("cdf97", torch.float16, False, 32),
                           ("cdf97", torch.float32, True, 16), ("cdf97", torch.bfloat16, True, 24),
-                          ("cdf53", torch.float16, True, 3), ("cdf53", torch.bfloat16, True, 8)])
+                          ("cdf53", torch.float16, True, 3), ("cdf53", torch.bfloat16, True, 11)])
 def test_both_sides_of_the_line(wavelet, dtype, inverse, eighths):
     """Launches of exactly the windows of the line, and of one more."""
     windows = eighths * _cus() // 8
