@@ -121,10 +121,10 @@ bool cross_conflict(std::vector<Access> &v) {
     return false;
 }
 
-bool aligned(const void *p, int64_t pitch, int dt, int vec_elems) {
-    size_t bytes = (size_t)vec_elems * elem_size(dt);
-    if (bytes > 16) bytes = 16;
-    return ((uintptr_t)p % bytes) == 0 && ((size_t)pitch * elem_size(dt)) % bytes == 0;
+// Whether every row of a buffer starts at a 32-bit word: what vector accesses
+// of up to 16 bytes need (wider alignment measured no faster).
+bool word_rows(const void *p, int64_t pitch, int dt) {
+    return elem_size(dt) == 4 || ((uintptr_t)p % 4 == 0 && pitch % 2 == 0);
 }
 
 int pairs_of(int wavelet) { return wavelet == DWT2_CDF97 ? 2 : 1; }
@@ -318,7 +318,8 @@ TailPlan plan_inv_tail(int F, int wavelet, int nqx_first, int nqy_first) {
 // with 270). So for c = 1..4 workgroups per CU the smallest segment whose grid
 // has at most c per CU is weighed, at the time its row pairs take: measured
 // 0.97, 1.8, 2.85, 3.5 us each with c = 1, 2, 3, 4 workgroups on a CU in FP32,
-// 0.83, 1.23, 1.75, 2.3 with 16-bit storage, whatever the image. Forward, us
+// 0.83, 1.23, 1.75, 2.3 with 16-bit storage, whatever the image (FP32 with
+// streamed output 1.7 at c = 2: 5504^2 inverse 53.0 us against 57.9 at c = 1). Forward, us
 // with c = 1, 2, 3, 4: FP32 2048^2 12.8, 14.6 and 7680x4320 56.1, 60.0, 62.5,
 // 63.3; 16-bit 2048^2 12.5, 13.4, 4096^2 27.7, 25.1, 27.7 and 7680x4320 47.5,
 // 40.2, 39.7, 44.3. With eight or more workgroups per CU the grid evens out by
@@ -334,8 +335,10 @@ int64_t head_tasks(const HeadShape *im, int n, int seg) {
         t += (int64_t)((im[i].nqx + kHeadOwn - 1) / kHeadOwn) * ((im[i].nqy + seg - 1) / seg);
     return t;
 }
-int head_segment(const HeadShape *im, int n, int wavelet, bool wide, bool inverse) {
+int head_segment(const HeadShape *im, int n, int wavelet, bool wide, bool inverse,
+                 bool streamed) {
     static const double kPairTime[2][4] = {{0.83, 1.23, 1.75, 2.3}, {0.97, 1.8, 2.85, 3.5}};
+    const double kPairTimeStream2 = 1.7;
     const int64_t cus = device_cus();
     const int many = !wide ? 18 : inverse ? 15 : 9;
     if (head_tasks(im, n, many) >= 8 * kHeadWaves * cus) return many;
@@ -351,7 +354,8 @@ int head_segment(const HeadShape *im, int n, int wavelet, bool wide, bool invers
             if (head_tasks(im, n, mid) <= c * kHeadWaves * cus) hi = mid; else lo = mid + 1;
         }
         const int pairs = (lo + halo + D - 1) / D * D;   // whole groups of D
-        const double cost = pairs * kPairTime[wide][c - 1];
+        const double cost =
+            pairs * (wide && streamed && c == 2 ? kPairTimeStream2 : kPairTime[wide][c - 1]);
         if (best == 0 || cost < best) {
             best = cost;
             seg = std::min(pairs - halo, tallest);
@@ -375,52 +379,64 @@ int64_t head_windows(const HeadShape &im, bool inverse) {
 //   9/7 forward FP32: 75 windows 8.6, 9.2 (8.8, 9.3); 504: 13.8, 16.0 (17.9, 19.7);
 //     602: 17.7, 16.3 (23.7, 21.4); 261, in between: 12.2, 11.9 (14.5, 12.8)
 //   9/7 forward 16-bit: 240: 9.7, 12.2 (11.4, 12.3); 774: 18.8, 19.7 (21.5, 21.0);
+//     1026: 22.1, 23.1 (25.6, 24.9);
 //     1368: 26.4, 25.2 (32.5, 28.3)
 //   9/7 inverse FP32: 60: 8.6, 9.6 (8.9, 9.6); 490: 14.7, 17.3 (20.7, 21.7);
 //     630: 20.7, 20.3 (29.3, 27.3)
 //   9/7 inverse 16-bit: 216: 9.6, 12.8 (11.3, 13.1); 630: 18.9, 20.6 (23.2, 21.5);
-//     846: 23.1, 24.0 (29.8, 24.9)
+//     846: 23.1, 24.0 (29.8, 24.9); with streamed pixels, 630: 16.6, 19.7 (19.0, 20.1),
+//     954: 20.5, 24.8 (24.4, 25.9), 1512: 29.4, 31.9 (36.5, 35.4), 1890: 35.7, 34.5
+//     (47.1, 38.1)
 // The 5/3 strips carry half the stages and less halo, and are faster at every
 // size (forward: see kFwdByWindows; inverse FP32 72: 7.5, 6.2 (8.4, 6.5), 490: 13.8,
 // 13.6 (20.7, 19.7)) but one: 16-bit inverse, 72: 7.4, 6.3 (7.7, 6.3); 117: 7.6,
 // 8.0 (7.9, 8.0); 216: 8.3, 10.1 (10.1, 10.6); 342: 10.2, 11.0; 360: 11.9, 11.0
 // (14.8, 12.2).
-bool head_by_windows(const HeadShape *im, int n, int wavelet, bool wide, bool inverse) {
+// FP32 9/7 forward strips whose band rows are off the 64-byte sectors write parts
+// of lines at every piece end, and lose to windows again where those are many:
+// pitch of 28 bytes more, 1026 windows: 35.6, 34.4; 1848: 58.3, 61.7; 4104: 112.9,
+// 123.3; 15848 x 16384: 445, 462 (16384^2, on lines: 474, 403).
+bool head_by_windows(const HeadShape *im, int n, int wavelet, bool wide, bool inverse,
+                     bool streamed, bool off_sectors) {
     const int64_t cus = device_cus();
     int64_t w = 0;
     for (int i = 0; i < n; ++i) w += head_windows(im[i], inverse);
-    if (wavelet == DWT2_CDF97) return w <= cus * (wide ? 2 : inverse ? 3 : 4);
+    if (wavelet == DWT2_CDF97 && wide && !inverse && off_sectors && w > 6 * cus) return true;
+    if (wavelet == DWT2_CDF97) return w <= cus * (wide ? 2 : !inverse ? 5 : streamed ? 6 : 3);
     return inverse && !wide && 8 * w > 3 * cus && 8 * w <= 11 * cus;
 }
-// The rows per segment of a head launch, or 0 where it runs by windows.
-int head_layout(const HeadShape *im, int n, int wavelet, bool wide, bool inverse) {
-    return head_by_windows(im, n, wavelet, wide, inverse)
-               ? 0 : head_segment(im, n, wavelet, wide, inverse);
+// Whether pixel or level j band rows of a head may start at odd halves of a word.
+bool head_odd(const FwdHead &h) { return !(h.l1.vec_in && h.l1.vec_band); }
+bool head_odd(const InvHead &h) { return !(h.l1.vec_band && h.l1.vec_out); }
+// Whether level j band rows start off the 64-byte sectors (forward).
+bool head_off_sectors(const FwdHead &h) {
+    const size_t pitch = (size_t)h.l1.band_pitch * 4;   // looked at for FP32 only
+    return (((uintptr_t)h.l1.hl | (uintptr_t)h.l1.lh | (uintptr_t)h.l1.hh | pitch) & 63) != 0;
+}
+bool head_off_sectors(const InvHead &) { return false; }
+// The rows per segment of a head launch, or 0 where it runs by windows, which
+// take rows at words only. odd: head_odd of any of the launch's images.
+int head_layout(const HeadShape *im, int n, int wavelet, bool wide, bool inverse, bool odd,
+                bool streamed = false, bool off_sectors = false) {
+    return !odd && head_by_windows(im, n, wavelet, wide, inverse, streamed, off_sectors)
+               ? 0 : head_segment(im, n, wavelet, wide, inverse, streamed);
 }
 
 // Layout of one image's head in a launch, by windows (seg 0) or strips; its
-// number of tasks. A head's accesses need word alignment only, also the 8- and
-// 16-byte ones.
-void head_alignment(FwdHead &hd, int dt) {
-    hd.l1.vec_in = aligned(hd.l1.in, hd.l1.in_pitch, dt, dt == DWT2_F32 ? 1 : 2);
-}
-void head_alignment(InvHead &hd, int dt) {
-    hd.l1.vec_out = aligned(hd.l1.out, hd.l1.out_pitch, dt, dt == DWT2_F32 ? 1 : 2);
-}
-// full_dt: type of level j's input (forward) or output (inverse).
+// number of tasks.
 template <typename H>
-int head_grid(H &hd, int seg, int full_dt) {
+int head_grid(H &hd, int seg) {
     constexpr int X = HeadWindow::FOX2;
-    head_alignment(hd, full_dt);
     hd.seg = seg;
     hd.across = seg ? (hd.l2.nqx + kHeadOwn - 1) / kHeadOwn : (hd.l2.nqx + X - 1) / X;
     const HeadShape im{hd.l2.nqx, hd.l2.nqy};
     return (int)(seg ? head_tasks(&im, 1, seg) : head_windows(im, std::is_same<H, InvHead>::value));
 }
 template <typename H>
-int head_grid_one(H &hd, int wavelet, int dt, bool inverse) {
+int head_grid_one(H &hd, int wavelet, int dt, bool inverse, bool streamed) {
     const HeadShape im{hd.l2.nqx, hd.l2.nqy};
-    return head_grid(hd, head_layout(&im, 1, wavelet, dt == DWT2_F32, inverse), dt);
+    return head_grid(hd, head_layout(&im, 1, wavelet, dt == DWT2_F32, inverse, head_odd(hd),
+                                     streamed, head_off_sectors(hd)));
 }
 
 // Size class of a level whose input is width x height pixels.
@@ -453,11 +469,10 @@ FwdParams fwd_params(const void *in, int64_t in_pitch, int in_dt, int width, int
     p.w = width; p.h = height; p.nqx = nqx; p.nqy = nqy;
     const Plan pl = plan_level(tile, wavelet, nqx, nqy);
     p.tiles_x = pl.tiles_x; p.tiles_y = pl.tiles_y;
-    const int q = kTiles[tile].qpl;
-    p.vec_in = aligned(in, in_pitch, in_dt, 2 * q);
-    p.vec_ll = aligned(ll, ll_pitch, ll_dt, q);
-    p.vec_band = aligned(hl, band_pitch, band_dt, q) && aligned(lh, band_pitch, band_dt, q) &&
-                 aligned(hh, band_pitch, band_dt, q);
+    p.vec_in = word_rows(in, in_pitch, in_dt);
+    p.vec_ll = word_rows(ll, ll_pitch, ll_dt);
+    p.vec_band = word_rows(hl, band_pitch, band_dt) && word_rows(lh, band_pitch, band_dt) &&
+                 word_rows(hh, band_pitch, band_dt);
     return p;
 }
 
@@ -473,11 +488,10 @@ InvParams inv_params(const void *ll, int64_t ll_pitch, int ll_dt, const void *hl
     p.w = width; p.h = height; p.nqx = nqx; p.nqy = nqy;
     const Plan pl = plan_level(tile, wavelet, nqx, nqy);
     p.tiles_x = pl.tiles_x; p.tiles_y = pl.tiles_y;
-    const int q = kTiles[tile].qpl;
-    p.vec_ll = aligned(ll, ll_pitch, ll_dt, q);
-    p.vec_band = aligned(hl, band_pitch, band_dt, q) && aligned(lh, band_pitch, band_dt, q) &&
-                 aligned(hh, band_pitch, band_dt, q);
-    p.vec_out = aligned(out, out_pitch, out_dt, 2 * q);
+    p.vec_ll = word_rows(ll, ll_pitch, ll_dt);
+    p.vec_band = word_rows(hl, band_pitch, band_dt) && word_rows(lh, band_pitch, band_dt) &&
+                 word_rows(hh, band_pitch, band_dt);
+    p.vec_out = word_rows(out, out_pitch, out_dt);
     p.stream_out = 0;
     return p;
 }
@@ -647,6 +661,15 @@ const PlanLaunch *plan_launches(const PlanHeader *h) {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// odd_rows of any image of a level launch (plan: its host copy).
+template <typename P>
+bool any_odd_rows(const void *plan, const PlanLaunch &l) {
+    const P *p = reinterpret_cast<const P *>(static_cast<const char *>(plan) + l.off_params);
+    bool odd = false;
+    for (int i = 0; i < l.images; ++i) odd |= odd_rows(p[i]);
+    return odd;
+}
+
 // The strip section of a head launch.
 size_t head_param_size(int inverse) { return inverse ? sizeof(InvHead) : sizeof(FwdHead); }
 size_t off_strips(const PlanLaunch &l, int inverse) {
@@ -757,17 +780,12 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
         G.l.f32_b = inverse ? dtype == DWT2_F32 : ll2_f32;
         std::vector<HeadShape> shapes(n);
         for (int i = 0; i < n; ++i) shapes[i] = {images[i].width / 4, images[i].height / 4};
-        // one layout and segment height for the launch: its workgroups hold
-        // strips of several images
-        const int seg = head_layout(shapes.data(), n, wavelet, dtype == DWT2_F32, inverse);
-        if (seg && head_tasks(shapes.data(), n, seg) > (int64_t)INT32_MAX - kHeadWaves)
-            return DWT2_ERR_INVALID_ARG;
+        bool odd = false;
         for (int i = 0; i < n; ++i) {
             const dwt2_image &im = images[i];
             const int W = im.width, H = im.height;
             float *ws0 = static_cast<float *>(im.workspace);
             float *ws1 = ws0 + (size_t)(W / 2) * (H / 2);
-            int tasks;
             if (inverse) {
                 const char *cb = static_cast<const char *>(im.src);
                 const int64_t cp = im.src_pitch;
@@ -781,7 +799,7 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
                                    cb + (size_t)((int64_t)(H / 2) * cp) * es,
                                    cb + (size_t)((int64_t)(H / 2) * cp + W / 2) * es, cp, dtype,
                                    im.dst, im.dst_pitch, dtype, W, H, wavelet, 0);
-                tasks = head_grid(hd, seg, dtype);
+                odd |= head_odd(hd);
                 G.ih.push_back(hd);
             } else {
                 char *cb = static_cast<char *>(im.dst);
@@ -797,9 +815,17 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
                                    cb + (size_t)((int64_t)(H / 4) * cp) * es,
                                    cb + (size_t)((int64_t)(H / 4) * cp + W / 4) * es, cp, dtype,
                                    wavelet, 0);
-                tasks = head_grid(hd, seg, dtype);
+                odd |= head_odd(hd);
                 G.fh.push_back(hd);
             }
+        }
+        // one layout and segment height for the launch: its workgroups hold
+        // strips of several images
+        const int seg = head_layout(shapes.data(), n, wavelet, dtype == DWT2_F32, inverse, odd);
+        if (seg && head_tasks(shapes.data(), n, seg) > (int64_t)INT32_MAX - kHeadWaves)
+            return DWT2_ERR_INVALID_ARG;
+        for (int i = 0; i < n; ++i) {
+            const int tasks = inverse ? head_grid(G.ih[i], seg) : head_grid(G.fh[i], seg);
             if (seg) {
                 G.strip_start.push_back((int32_t)G.strip_img.size());
                 G.strip_img.insert(G.strip_img.end(), (size_t)tasks, (int32_t)i);
@@ -1105,15 +1131,15 @@ int dwt2_forward_ex(const void *src, const dwt2_desc *src_d, void *coef, const d
         if (j >= k) {   // fused: parameters only (the kernel reads in of the first, ll of the last)
             tail.lv[j - k] = fwd_params(in, in_pitch, in_dt, w, h, ll, ll_pitch, ll_dt, hl, lh,
                                         hh, cp, T, wavelet, 0);
-            tail.lv[j - k].vec_in = aligned(in, in_pitch, in_dt, 2);
+            tail.lv[j - k].vec_in = word_rows(in, in_pitch, in_dt);
             continue;
         }
         if (head && j <= 2) {   // levels 1 and 2: one launch once both are planned
             (j == 1 ? hd.l1 : hd.l2) = fwd_params(in, in_pitch, in_dt, w, h, ll, ll_pitch, ll_dt,
                                                   hl, lh, hh, cp, T, wavelet, 0);
             if (j == 1) continue;
-            const int tasks = head_grid_one(hd, wavelet, T, false);
             const bool stream_bands = (int64_t)W * H * (int64_t)es > kCacheBytes;
+            const int tasks = head_grid_one(hd, wavelet, T, false, stream_bands);
             if ((st = record(level_events, 0, s))) return st;
             const hipError_t e =
                 fwd_head_table(T)[wavelet][scheme][T == DWT2_F32][levels > 2 || T == DWT2_F32](
@@ -1194,9 +1220,9 @@ int dwt2_inverse_ex(const void *coef, const dwt2_desc *coef_d, void *dst, const 
             InvParams &p = tail.lv[levels - j];
             p = inv_params(ll, ll_pitch, ll_dt, hl, lh, hh, cp, T, out, out_pitch, out_dt, w, h,
                            wavelet, 0);
-            p.vec_ll = aligned(ll, ll_pitch, ll_dt, 1);
-            p.vec_band = aligned(hl, cp, T, 1) && aligned(lh, cp, T, 1) && aligned(hh, cp, T, 1);
-            p.vec_out = aligned(out, out_pitch, out_dt, 2);
+            p.vec_ll = word_rows(ll, ll_pitch, ll_dt);
+            p.vec_band = word_rows(hl, cp, T) && word_rows(lh, cp, T) && word_rows(hh, cp, T);
+            p.vec_out = word_rows(out, out_pitch, out_dt);
             if (j > k) continue;
             const int F = levels + 1 - k;
             const TailPlan pl = plan_inv_tail(F, wavelet, tail.lv[0].nqx, tail.lv[0].nqy);
@@ -1225,11 +1251,13 @@ int dwt2_inverse_ex(const void *coef, const dwt2_desc *coef_d, void *dst, const 
             (j == 2 ? hd.l2 : hd.l1) = inv_params(ll, ll_pitch, ll_dt, hl, lh, hh, cp, T, out,
                                                   out_pitch, out_dt, w, h, wavelet, 0);
             if (j == 2) continue;
-            const int tasks = head_grid_one(hd, wavelet, T, true);
+            const bool stream_pixels = image_bytes >= kStreamOutMinBytes;
+            hd.l1.stream_out = stream_pixels;
+            const int tasks = head_grid_one(hd, wavelet, T, true, stream_pixels);
             if ((st = record(level_events, 0, s))) return st;
             const hipError_t e =
                 inv_head_table(T)[wavelet][scheme][levels > 2 || T == DWT2_F32][T == DWT2_F32](
-                    hd, tasks, image_bytes >= kStreamOutMinBytes, s);
+                    hd, tasks, stream_pixels, s);
             if (e != hipSuccess) return hip_fail(e);
             for (int ev = 1; ev <= 3; ++ev)
                 if ((st = record(level_events, ev, s))) return st;
@@ -1336,14 +1364,14 @@ int dwt2_batch_run(const void *plan, size_t plan_bytes, const void *plan_device,
                                       reinterpret_cast<const InvParams *>(dev + l.off_params),
                                       l.total};
             e = inv_plan_table(h->dtype)[h->wavelet][scheme][l.f32_a][l.f32_b][l.tile](
-                tl, persistent, stream);
+                tl, any_odd_rows<InvParams>(plan, l), persistent, stream);
         } else {
             TableLaunch<FwdParams> tl{reinterpret_cast<const int32_t *>(dev + l.off_img),
                                       reinterpret_cast<const int32_t *>(dev + l.off_start),
                                       reinterpret_cast<const FwdParams *>(dev + l.off_params),
                                       l.total};
             e = fwd_plan_table(h->dtype)[h->wavelet][scheme][l.f32_a][l.f32_b][l.tile](
-                tl, persistent, stream);
+                tl, any_odd_rows<FwdParams>(plan, l), persistent, stream);
         }
         if (e != hipSuccess) return hip_fail(e);
     }
@@ -1512,7 +1540,6 @@ int head_batch(const dwt2_level_job *jobs, int32_t n, int32_t wavelet, int32_t s
     for (int g = 0; g < n && st == DWT2_OK; ++g) {   // one group per distinct key
         if (done[g]) continue;
         const HeadKey key = keys[g];
-        const int full_dt = jobs[2 * g].full_dtype;   // FP32 or the band type, by the key
         typename std::conditional<INV, InvHeadBatch, FwdHeadBatch>::type b;
         HeadShape shapes[kHeadBatchMax];
         b.n = 0;
@@ -1544,13 +1571,16 @@ int head_batch(const dwt2_level_job *jobs, int32_t n, int32_t wavelet, int32_t s
             if (b.n > 0 && (b.n == kHeadBatchMax || i == n)) {
                 // one layout and segment height for the launch: its workgroups
                 // hold strips of several images
-                const int seg = head_layout(shapes, b.n, wavelet, key.band_dt == DWT2_F32, INV);
+                bool odd = false;
+                for (int k = 0; k < b.n; ++k) odd |= head_odd(b.h[k]);
+                const int seg =
+                    head_layout(shapes, b.n, wavelet, key.band_dt == DWT2_F32, INV, odd);
                 if (seg && head_tasks(shapes, b.n, seg) > (int64_t)INT32_MAX - kHeadWaves) {
                     st = DWT2_ERR_INVALID_ARG;
                     break;
                 }
                 for (int k = 0; k < b.n; ++k)
-                    b.tile_start[k + 1] = b.tile_start[k] + head_grid(b.h[k], seg, full_dt);
+                    b.tile_start[k + 1] = b.tile_start[k] + head_grid(b.h[k], seg);
                 hipError_t e;
                 if constexpr (INV)
                     e = inv_head_batch_table(key.band_dt)[wavelet][scheme][key.a_f32][key.b_f32](

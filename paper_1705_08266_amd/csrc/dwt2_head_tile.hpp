@@ -42,7 +42,8 @@
 
 namespace dwt2 {
 
-// 12 wavefronts of 4 quad rows.
+// 12 wavefronts of 4 quad rows. Every row starts at a word (2-byte rows at odd
+// halves go by strips).
 constexpr int kHeadTileRows = 4, kHeadTileWaves = 12;
 
 template <int ROWS, int WAVES>
@@ -120,7 +121,7 @@ __device__ __forceinline__ void fwd_head_tile(const FwdHead &hd, const int t,
         const int qx = 2 * (ox2 - RG - 1 + lane);       // the lane's first quad column
         const int qy0 = 2 * oy2 - 3 * RG + wave * ROWS; // its first quad row
         Quads<ROWS, 2> q;
-        fwd_load_at<2, ROWS, TIN>(q, p1, qx, qy0);
+        fwd_load_at<2, ROWS, TIN, false>(q, p1, qx, qy0);
         {
             Exchange<ROWS, 2, WAVES> x{&box, wave, lane, 0};
             lift_forward<WV, SCH>(q, x);
@@ -145,8 +146,6 @@ __device__ __forceinline__ void fwd_head_tile(const FwdHead &hd, const int t,
         TB *hl = static_cast<TB *>(p1.hl);
         TB *lh = static_cast<TB *>(p1.lh);
         TB *hh = static_cast<TB *>(p1.hh);
-        const uint32_t bb = (uint32_t)p1.nqx * (uint32_t)sizeof(TB);
-        const uint32_t off = own_x ? (uint32_t)qx * (uint32_t)sizeof(TB) : kNoAccess;
         int64_t rowo = (int64_t)qy0 * p1.band_pitch;   // band row qy0 + r, stepped
 #pragma unroll
         for (int r = 0; r < ROWS; ++r, rowo += p1.band_pitch) {
@@ -156,19 +155,9 @@ __device__ __forceinline__ void fwd_head_tile(const FwdHead &hd, const int t,
             const float vb[2] = {q.b[r][0] * sHL, q.b[r][1] * sHL};
             const float vc[2] = {q.c[r][0] * sHL, q.c[r][1] * sHL};
             const float vd[2] = {q.d[r][0] * sHH, q.d[r][1] * sHH};
-            if (p1.vec_band) {
-                store_vec<TB, 2>(make_rsrc(hl + rowo, bb), off, vb);
-                store_vec<TB, 2>(make_rsrc(lh + rowo, bb), off, vc);
-                store_vec<TB, 2>(make_rsrc(hh + rowo, bb), off, vd);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const uint32_t oi = own_x ? off + (uint32_t)(i * sizeof(TB)) : kNoAccess;
-                    store_elem<TB>(make_rsrc(hl + rowo, bb), oi, vb[i]);
-                    store_elem<TB>(make_rsrc(lh + rowo, bb), oi, vc[i]);
-                    store_elem<TB>(make_rsrc(hh + rowo, bb), oi, vd[i]);
-                }
-            }
+            store_cols<TB, 2>(hl + rowo, p1.nqx, qx, own_x, true, vb);
+            store_cols<TB, 2>(lh + rowo, p1.nqx, qx, own_x, true, vc);
+            store_cols<TB, 2>(hh + rowo, p1.nqx, qx, own_x, true, vd);
         }
     }
 
@@ -249,7 +238,7 @@ __device__ __forceinline__ void inv_head_tile(const InvHead &hd, const int t,
     // ---- level j+1: window of 64 x H2 quads, one per lane, R2 rows per wavefront
     if (wave * R2 < H2) {
         Quads<R2, 1> q;
-        inv_load_at<1, R2, TLL, TB>(q, hd.l2, c0 + lane, r0 + wave * R2);
+        inv_load_at<1, R2, TLL, TB, false>(q, hd.l2, c0 + lane, r0 + wave * R2);
 #pragma unroll
         for (int r = 0; r < R2; ++r) {
             q.a[r][0] *= uLL; q.b[r][0] *= uHL; q.c[r][0] *= uHL; q.d[r][0] *= uHH;
@@ -278,7 +267,7 @@ __device__ __forceinline__ void inv_head_tile(const InvHead &hd, const int t,
     const int qx = wx1 + 2 * lane;
     const int qy0 = wy1 + wave * ROWS;
     Quads<ROWS, 2> q;
-    inv_load_at<2, ROWS, TB, TB, false>(q, p1, qx, qy0);
+    inv_load_at<2, ROWS, TB, TB, false, false>(q, p1, qx, qy0);
     {
         // the low-low coefficient of quad (i, j) is the extended low phase
         int cx[2], px[2];
@@ -324,8 +313,7 @@ __device__ __forceinline__ void inv_head_tile(const InvHead &hd, const int t,
     const bool own_x = lane >= 1 && lane < 1 + G::IOX1 / 2;
     TOUT *out = static_cast<TOUT *>(p1.out);
     const int px0 = 2 * qx;
-    const bool full_x = own_x && p1.vec_out && px0 + 4 <= p1.w;
-    const uint32_t rb = (uint32_t)p1.w * (uint32_t)sizeof(TOUT);
+    const bool on = own_x && px0 < p1.w;
     int64_t ro = (int64_t)(2 * qy0) * p1.out_pitch;   // pixel row 2 (qy0 + r), stepped
 #pragma unroll
     for (int r = 0; r < ROWS; ++r, ro += 2 * p1.out_pitch) {
@@ -336,18 +324,12 @@ __device__ __forceinline__ void inv_head_tile(const InvHead &hd, const int t,
         const float o[4] = {q.c[r][0], q.d[r][0], q.c[r][1], q.d[r][1]};
         TOUT *r0p = out + ro;
         TOUT *r1p = r0p + p1.out_pitch;
-        if (p1.vec_out) {
-            const uint32_t off = full_x ? (uint32_t)px0 * (uint32_t)sizeof(TOUT) : kNoAccess;
-            store_vec<TOUT, 4>(make_rsrc(r0p, rb), off, e);
-            store_vec<TOUT, 4>(make_rsrc(r1p, rb), off, o);
-        } else if (own_x) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (px0 + k < p1.w) {
-                    r0p[px0 + k] = from_float<TOUT>(e[k]);
-                    r1p[px0 + k] = from_float<TOUT>(o[k]);
-                }
-            }
+        if (p1.stream_out) {
+            store_cols<TOUT, 4, kStoreStream>(r0p, p1.w, px0, on, true, e);
+            store_cols<TOUT, 4, kStoreStream>(r1p, p1.w, px0, on, true, o);
+        } else {
+            store_cols<TOUT, 4>(r0p, p1.w, px0, on, true, e);
+            store_cols<TOUT, 4>(r1p, p1.w, px0, on, true, o);
         }
     }
 }

@@ -23,7 +23,7 @@ struct FwdParams {
     int64_t band_pitch;
     int32_t w, h, nqx, nqy;
     int32_t tiles_x, tiles_y;
-    int32_t vec_in, vec_ll, vec_band;   // 1 when vector accesses are aligned
+    int32_t vec_in, vec_ll, vec_band;   // 1: every row starts at a 32-bit word
 };
 
 struct InvParams {
@@ -35,9 +35,16 @@ struct InvParams {
     int64_t out_pitch;
     int32_t w, h, nqx, nqy;
     int32_t tiles_x, tiles_y;
-    uint8_t vec_ll, vec_band, vec_out;   // 1 when vector accesses are aligned
+    uint8_t vec_ll, vec_band, vec_out;   // 1: every row starts at a 32-bit word
     uint8_t stream_out;                  // 1: vector output stores are non-temporal
 };
+
+// Whether a row of the level may start at the upper half of a word, which the
+// kernels with ODD set take (RowIn, store_cols): kernels of their own, since
+// in one with the word path their registers cost it wavefronts (4096^2 FP16
+// forward: 16.5 us alone, 18.4 with both).
+inline bool odd_rows(const FwdParams &p) { return !(p.vec_in && p.vec_ll && p.vec_band); }
+inline bool odd_rows(const InvParams &p) { return !(p.vec_ll && p.vec_band && p.vec_out); }
 
 // Geometry of a tile configuration. The horizontal halo is one lane's worth
 // of quads on each side (>= the number of lifting pairs), which keeps every
@@ -122,12 +129,12 @@ __device__ __forceinline__ float pick(const float (&a)[E], const float (&b)[E], 
 // Completes the loads of `n` rows for the lanes of an edge wavefront: the
 // second vector of each row, then the per-lane select. `v[r]` holds the
 // first vector on entry and the lane's elements on exit.
-template <typename T, int E, int N>
-__device__ __forceinline__ void fix_cols(const rsrc_t (&rows)[N], const EdgeCols<E> &c,
+template <typename T, int E, bool ODD, int N>
+__device__ __forceinline__ void fix_cols(const RowIn<T, E, ODD> (&rows)[N], const EdgeCols<E> &c,
                                          float (&v)[N][E]) {
     float b[N][E];
 #pragma unroll
-    for (int r = 0; r < N; ++r) load_vec<T, E>(rows[r], c.off_b, b[r]);
+    for (int r = 0; r < N; ++r) rows[r].load(c.off_b, b[r]);
 #pragma unroll
     for (int r = 0; r < N; ++r) {
         float a[E];
@@ -140,36 +147,19 @@ __device__ __forceinline__ void fix_cols(const rsrc_t (&rows)[N], const EdgeCols
 
 // The lane's quads start at quad column qx0 and quad row qy0 of the level;
 // positions outside the level are read through the symmetric extension.
-template <int QPL, int ROWS, typename TIN>
+// ODD: rows may start at the upper half of a word (2-byte elements).
+template <int QPL, int ROWS, typename TIN, bool ODD>
 __device__ __forceinline__ void fwd_load_at(Quads<ROWS, QPL> &q, const FwdParams &prm, int qx0,
                                             int qy0) {
     const TIN *in = static_cast<const TIN *>(prm.in);
     const int px0 = 2 * qx0;
-    // vector loads need aligned rows whose length is a multiple of the lane's
-    // E elements, so that no vector is partly outside the row
-    if (!prm.vec_in || (prm.w & (2 * QPL - 1)) != 0) {   // else one element at a time
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            const TIN *r0 = in + (int64_t)mirror(2 * (qy0 + r), prm.h) * prm.in_pitch;
-            const TIN *r1 = in + (int64_t)mirror(2 * (qy0 + r) + 1, prm.h) * prm.in_pitch;
-#pragma unroll
-            for (int i = 0; i < QPL; ++i) {
-                const int xe = mirror(px0 + 2 * i, prm.w);
-                const int xo = mirror(px0 + 2 * i + 1, prm.w);
-                q.a[r][i] = to_float(r0[xe]); q.b[r][i] = to_float(r0[xo]);
-                q.c[r][i] = to_float(r1[xe]); q.d[r][i] = to_float(r1[xo]);
-            }
-        }
-        return;
-    }
     int m[2 * QPL];
 #pragma unroll
     for (int k = 0; k < 2 * QPL; ++k) m[k] = mirror(px0 + k, prm.w);
     const EdgeCols<2 * QPL> cols = EdgeCols<2 * QPL>::template from<TIN>(
         m, px0, px0 >= 0 && px0 + 2 * QPL <= prm.w);
-    const uint32_t rb = (uint32_t)prm.w * (uint32_t)sizeof(TIN);
     // all rows' first vectors, then (edge wavefronts only) the completion
-    rsrc_t rows[2 * ROWS];
+    RowIn<TIN, 2 * QPL, ODD> rows[2 * ROWS];
     float v[2 * ROWS][2 * QPL];
     if (2 * qy0 >= 0 && 2 * (qy0 + ROWS) <= prm.h) {
         // all rows inside the level (wavefront-uniform): step the row pointer
@@ -178,21 +168,18 @@ __device__ __forceinline__ void fwd_load_at(Quads<ROWS, QPL> &q, const FwdParams
         const TIN *p = in + (int64_t)(2 * qy0) * prm.in_pitch;
 #pragma unroll
         for (int r = 0; r < 2 * ROWS; ++r) {
-            rows[r] = make_rsrc(p, rb);
-            load_vec<TIN, 2 * QPL>(rows[r], cols.off_a, v[r]);
+            rows[r].at(p, prm.w);
+            rows[r].load(cols.off_a, v[r]);
             p += prm.in_pitch;
         }
     } else {
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            const int py = 2 * (qy0 + r);
-            rows[2 * r] = make_rsrc(in + (int64_t)mirror(py, prm.h) * prm.in_pitch, rb);
-            rows[2 * r + 1] = make_rsrc(in + (int64_t)mirror(py + 1, prm.h) * prm.in_pitch, rb);
-            load_vec<TIN, 2 * QPL>(rows[2 * r], cols.off_a, v[2 * r]);
-            load_vec<TIN, 2 * QPL>(rows[2 * r + 1], cols.off_a, v[2 * r + 1]);
+        for (int r = 0; r < 2 * ROWS; ++r) {
+            rows[r].at(in + (int64_t)mirror(2 * qy0 + r, prm.h) * prm.in_pitch, prm.w);
+            rows[r].load(cols.off_a, v[r]);
         }
     }
-    if (!wave_all(cols.plain)) fix_cols<TIN>(rows, cols, v);
+    if (!wave_all(cols.plain)) fix_cols(rows, cols, v);
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
 #pragma unroll
@@ -202,16 +189,15 @@ __device__ __forceinline__ void fwd_load_at(Quads<ROWS, QPL> &q, const FwdParams
         }
     }
 }
-
-template <int QPL, int ROWS, typename G, typename TIN>
+template <int QPL, int ROWS, typename G, typename TIN, bool ODD>
 __device__ __forceinline__ void fwd_load(Quads<ROWS, QPL> &q, const FwdParams &prm, int t,
                                          int lane, int wave) {
     const int ty = t / prm.tiles_x, tx = t - (t / prm.tiles_x) * prm.tiles_x;
-    fwd_load_at<QPL, ROWS, TIN>(q, prm, tx * G::OX - G::HX + lane * QPL,
-                                ty * G::OY - G::HY + wave * ROWS);
+    fwd_load_at<QPL, ROWS, TIN, ODD>(q, prm, tx * G::OX - G::HX + lane * QPL,
+                                     ty * G::OY - G::HY + wave * ROWS);
 }
 
-template <int WV, int QPL, int ROWS, int WAVES, typename G, typename TLL, typename TB>
+template <int WV, int QPL, int ROWS, int WAVES, typename G, typename TLL, typename TB, bool ODD>
 __device__ __forceinline__ void fwd_store(const Quads<ROWS, QPL> &q, const FwdParams &prm, int t,
                                           int lane, int wave) {
     using L = Wavelet<WV>;
@@ -225,7 +211,6 @@ __device__ __forceinline__ void fwd_store(const Quads<ROWS, QPL> &q, const FwdPa
     TB *hl = static_cast<TB *>(prm.hl);
     TB *lh = static_cast<TB *>(prm.lh);
     TB *hh = static_cast<TB *>(prm.hh);
-    const bool full_x = qx0 + QPL <= prm.nqx;
     // element offsets of row qy0 + r, stepped
     int64_t rowb = (int64_t)qy0 * prm.band_pitch, rowl = (int64_t)qy0 * prm.ll_pitch;
 #pragma unroll
@@ -239,44 +224,23 @@ __device__ __forceinline__ void fwd_store(const Quads<ROWS, QPL> &q, const FwdPa
             va[i] = q.a[r][i] * sLL; vb[i] = q.b[r][i] * sHL;
             vc[i] = q.c[r][i] * sHL; vd[i] = q.d[r][i] * sHH;
         }
-        const int64_t ob = rowb + qx0;
-        const int64_t ol = rowl + qx0;
-        if (full_x && prm.vec_ll) {
-            store_vec<TLL, QPL>(make_rsrc(ll + rowl, (uint32_t)prm.nqx * (uint32_t)sizeof(TLL)),
-                                (uint32_t)qx0 * (uint32_t)sizeof(TLL), va);
-        } else {
-#pragma unroll
-            for (int i = 0; i < QPL; ++i)
-                if (qx0 + i < prm.nqx) ll[ol + i] = from_float<TLL>(va[i]);
-        }
-        if (full_x && prm.vec_band) {
-            const uint32_t bb = (uint32_t)prm.nqx * (uint32_t)sizeof(TB);
-            const uint32_t off = (uint32_t)qx0 * (uint32_t)sizeof(TB);
-            const int64_t rowo = rowb;
-            store_vec<TB, QPL>(make_rsrc(hl + rowo, bb), off, vb);
-            store_vec<TB, QPL>(make_rsrc(lh + rowo, bb), off, vc);
-            store_vec<TB, QPL>(make_rsrc(hh + rowo, bb), off, vd);
-        } else {
-#pragma unroll
-            for (int i = 0; i < QPL; ++i) {
-                if (qx0 + i < prm.nqx) {
-                    hl[ob + i] = from_float<TB>(vb[i]);
-                    lh[ob + i] = from_float<TB>(vc[i]);
-                    hh[ob + i] = from_float<TB>(vd[i]);
-                }
-            }
-        }
+        const bool on = qx0 < prm.nqx;
+        store_cols<TLL, QPL>(ll + rowl, prm.nqx, qx0, on, !ODD, va);
+        store_cols<TB, QPL>(hl + rowb, prm.nqx, qx0, on, !ODD, vb);
+        store_cols<TB, QPL>(lh + rowb, prm.nqx, qx0, on, !ODD, vc);
+        store_cols<TB, QPL>(hh + rowb, prm.nqx, qx0, on, !ODD, vd);
     }
 }
 
 // One tile of a forward level: load, lift, store. All waves of the
 // workgroup call it with the same tile (it contains workgroup barriers).
-template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TIN, typename TLL, typename TB>
+template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TIN, typename TLL, typename TB,
+          bool ODD>
 __device__ __forceinline__ void fwd_tile(const FwdParams &prm, int t, Mailbox<QPL, WAVES> &box,
                                          int lane, int wave) {
     using G = TileGeom<WV, QPL, ROWS, WAVES>;
     Quads<ROWS, QPL> q;
-    fwd_load<QPL, ROWS, G, TIN>(q, prm, t, lane, wave);
+    fwd_load<QPL, ROWS, G, TIN, ODD>(q, prm, t, lane, wave);
     if constexpr (SCH == NONSEP_LDS || SCH == SEP_LDS) {
         __shared__ HBox<ROWS, WAVES> hb;
         LdsExchange<ROWS, QPL, WAVES> x{&box, &hb, wave, lane, 0};
@@ -285,24 +249,26 @@ __device__ __forceinline__ void fwd_tile(const FwdParams &prm, int t, Mailbox<QP
         Exchange<ROWS, QPL, WAVES> x{&box, wave, lane, 0};
         lift_forward<WV, SCH>(q, x);
     }
-    fwd_store<WV, QPL, ROWS, WAVES, G, TLL, TB>(q, prm, t, lane, wave);
+    fwd_store<WV, QPL, ROWS, WAVES, G, TLL, TB, ODD>(q, prm, t, lane, wave);
 }
 
 // One tile per workgroup.
-template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TIN, typename TLL, typename TB>
+template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TIN, typename TLL, typename TB,
+          bool ODD>
 __global__ __launch_bounds__(64 * WAVES) void fwd_level_kernel(FwdParams prm) {
     __shared__ Mailbox<QPL, WAVES> box;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform per wavefront
-    fwd_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB>(prm, block_tile(), box, lane, wave);
+    fwd_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB, ODD>(prm, block_tile(), box, lane, wave);
 }
 
 // ---- inverse ---------------------------------------------------------------------
 // Outside the level, each polyphase component is extended through the
 // symmetric extension of the pixel grid it lives on: quad (i, j) component b
 // stands for pixel (2i+1, 2j), and so on.
-// WITH_LL false: the detail bands only (q.a is left as it is).
-template <int QPL, int ROWS, typename TLL, typename TB, bool WITH_LL = true>
+// WITH_LL false: the detail bands only (q.a is left as it is). ODD: rows may
+// start at the upper half of a word (2-byte elements).
+template <int QPL, int ROWS, typename TLL, typename TB, bool ODD, bool WITH_LL = true>
 __device__ __forceinline__ void inv_load_at(Quads<ROWS, QPL> &q, const InvParams &prm, int qx0,
                                             int qy0) {
     const TLL *ll = static_cast<const TLL *>(prm.ll);
@@ -316,29 +282,12 @@ __device__ __forceinline__ void inv_load_at(Quads<ROWS, QPL> &q, const InvParams
         xe[i] = mirror(2 * (qx0 + i), prm.w) >> 1;
         xo[i] = (mirror(2 * (qx0 + i) + 1, prm.w) - 1) >> 1;
     }
-    if (!(prm.vec_ll && prm.vec_band) || (prm.nqx & (QPL - 1)) != 0) {   // one at a time
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            const int gy = qy0 + r;
-            const int ye = mirror(2 * gy, prm.h) >> 1;
-            const int yo = (mirror(2 * gy + 1, prm.h) - 1) >> 1;
-#pragma unroll
-            for (int i = 0; i < QPL; ++i) {
-                if constexpr (WITH_LL) q.a[r][i] = to_float(ll[(int64_t)ye * prm.ll_pitch + xe[i]]);
-                q.b[r][i] = to_float(hl[(int64_t)ye * prm.band_pitch + xo[i]]);
-                q.c[r][i] = to_float(lh[(int64_t)yo * prm.band_pitch + xe[i]]);
-                q.d[r][i] = to_float(hh[(int64_t)yo * prm.band_pitch + xo[i]]);
-            }
-        }
-        return;
-    }
     const bool plain = qx0 >= 0 && qx0 + QPL <= prm.nqx;
     const EdgeCols<QPL> ce = EdgeCols<QPL>::template from<TB>(xe, qx0, plain);
     const EdgeCols<QPL> co = EdgeCols<QPL>::template from<TB>(xo, qx0, plain);
     const EdgeCols<QPL> cl = EdgeCols<QPL>::template from<TLL>(xe, qx0, plain);
-    const uint32_t bb = (uint32_t)prm.nqx * (uint32_t)sizeof(TB);
-    const uint32_t lb = (uint32_t)prm.nqx * (uint32_t)sizeof(TLL);
-    rsrc_t rl[ROWS], rh[ROWS], rv[ROWS], rd[ROWS];   // LL, HL, LH, HH rows
+    RowIn<TLL, QPL, ODD> rl[ROWS];                             // LL rows
+    RowIn<TB, QPL, ODD> rh[ROWS], rv[ROWS], rd[ROWS];          // HL, LH, HH rows
     if (qy0 >= 0 && 2 * (qy0 + ROWS) <= prm.h) {
         // all rows inside the level (wavefront-uniform): both phases of quad
         // row gy are band row gy; step the row pointers
@@ -347,14 +296,14 @@ __device__ __forceinline__ void inv_load_at(Quads<ROWS, QPL> &q, const InvParams
         const TB *ph = hl + ob, *pv = lh + ob, *pd = hh + ob;
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            if constexpr (WITH_LL) rl[r] = make_rsrc(pl, lb);
-            rh[r] = make_rsrc(ph, bb);
-            rv[r] = make_rsrc(pv, bb);
-            rd[r] = make_rsrc(pd, bb);
-            if constexpr (WITH_LL) load_vec<TLL, QPL>(rl[r], cl.off_a, q.a[r]);
-            load_vec<TB, QPL>(rh[r], co.off_a, q.b[r]);
-            load_vec<TB, QPL>(rv[r], ce.off_a, q.c[r]);
-            load_vec<TB, QPL>(rd[r], co.off_a, q.d[r]);
+            if constexpr (WITH_LL) rl[r].at(pl, prm.nqx);
+            rh[r].at(ph, prm.nqx);
+            rv[r].at(pv, prm.nqx);
+            rd[r].at(pd, prm.nqx);
+            if constexpr (WITH_LL) rl[r].load(cl.off_a, q.a[r]);
+            rh[r].load(co.off_a, q.b[r]);
+            rv[r].load(ce.off_a, q.c[r]);
+            rd[r].load(co.off_a, q.d[r]);
             pl += prm.ll_pitch; ph += prm.band_pitch; pv += prm.band_pitch; pd += prm.band_pitch;
         }
     } else {
@@ -363,33 +312,32 @@ __device__ __forceinline__ void inv_load_at(Quads<ROWS, QPL> &q, const InvParams
             const int gy = qy0 + r;
             const int64_t ye = mirror(2 * gy, prm.h) >> 1;
             const int64_t yo = (mirror(2 * gy + 1, prm.h) - 1) >> 1;
-            if constexpr (WITH_LL) rl[r] = make_rsrc(ll + ye * prm.ll_pitch, lb);
-            rh[r] = make_rsrc(hl + ye * prm.band_pitch, bb);
-            rv[r] = make_rsrc(lh + yo * prm.band_pitch, bb);
-            rd[r] = make_rsrc(hh + yo * prm.band_pitch, bb);
-            if constexpr (WITH_LL) load_vec<TLL, QPL>(rl[r], cl.off_a, q.a[r]);
-            load_vec<TB, QPL>(rh[r], co.off_a, q.b[r]);
-            load_vec<TB, QPL>(rv[r], ce.off_a, q.c[r]);
-            load_vec<TB, QPL>(rd[r], co.off_a, q.d[r]);
+            if constexpr (WITH_LL) rl[r].at(ll + ye * prm.ll_pitch, prm.nqx);
+            rh[r].at(hl + ye * prm.band_pitch, prm.nqx);
+            rv[r].at(lh + yo * prm.band_pitch, prm.nqx);
+            rd[r].at(hh + yo * prm.band_pitch, prm.nqx);
+            if constexpr (WITH_LL) rl[r].load(cl.off_a, q.a[r]);
+            rh[r].load(co.off_a, q.b[r]);
+            rv[r].load(ce.off_a, q.c[r]);
+            rd[r].load(co.off_a, q.d[r]);
         }
     }
     if (!wave_all(plain)) {
-        if constexpr (WITH_LL) fix_cols<TLL>(rl, cl, q.a);
-        fix_cols<TB>(rh, co, q.b);
-        fix_cols<TB>(rv, ce, q.c);
-        fix_cols<TB>(rd, co, q.d);
+        if constexpr (WITH_LL) fix_cols(rl, cl, q.a);
+        fix_cols(rh, co, q.b);
+        fix_cols(rv, ce, q.c);
+        fix_cols(rd, co, q.d);
     }
 }
-
-template <int QPL, int ROWS, typename G, typename TLL, typename TB>
+template <int QPL, int ROWS, typename G, typename TLL, typename TB, bool ODD>
 __device__ __forceinline__ void inv_load(Quads<ROWS, QPL> &q, const InvParams &prm, int t,
                                          int lane, int wave) {
     const int ty = t / prm.tiles_x, tx = t - (t / prm.tiles_x) * prm.tiles_x;
-    inv_load_at<QPL, ROWS, TLL, TB>(q, prm, tx * G::OX - G::HX + lane * QPL,
-                                    ty * G::OY - G::HY + wave * ROWS);
+    inv_load_at<QPL, ROWS, TLL, TB, ODD>(q, prm, tx * G::OX - G::HX + lane * QPL,
+                                         ty * G::OY - G::HY + wave * ROWS);
 }
 
-template <int QPL, int ROWS, int WAVES, typename G, typename TOUT>
+template <int QPL, int ROWS, int WAVES, typename G, typename TOUT, bool ODD>
 __device__ __forceinline__ void inv_store(const Quads<ROWS, QPL> &q, const InvParams &prm, int t,
                                           int lane, int wave) {
     if (lane == 0 || lane == 63) return;   // halo lanes
@@ -398,7 +346,7 @@ __device__ __forceinline__ void inv_store(const Quads<ROWS, QPL> &q, const InvPa
     const int qy0 = ty * G::OY - G::HY + wave * ROWS;
     TOUT *out = static_cast<TOUT *>(prm.out);
     const int px0 = 2 * qx0;
-    const bool full_x = prm.vec_out && px0 + 2 * QPL <= prm.w;
+    const bool on = px0 < prm.w;
     int64_t ro = (int64_t)(2 * qy0) * prm.out_pitch;   // pixel row 2 (qy0 + r), stepped
 #pragma unroll
     for (int r = 0; r < ROWS; ++r, ro += 2 * prm.out_pitch) {
@@ -413,29 +361,18 @@ __device__ __forceinline__ void inv_store(const Quads<ROWS, QPL> &q, const InvPa
         }
         TOUT *r0 = out + ro;
         TOUT *r1 = r0 + prm.out_pitch;
-        if (full_x) {
-            const uint32_t rb = (uint32_t)prm.w * (uint32_t)sizeof(TOUT);
-            const uint32_t off = (uint32_t)px0 * (uint32_t)sizeof(TOUT);
-            if (prm.stream_out) {
-                store_vec<TOUT, 2 * QPL, kStoreStream>(make_rsrc(r0, rb), off, e);
-                store_vec<TOUT, 2 * QPL, kStoreStream>(make_rsrc(r1, rb), off, o);
-            } else {
-                store_vec<TOUT, 2 * QPL>(make_rsrc(r0, rb), off, e);
-                store_vec<TOUT, 2 * QPL>(make_rsrc(r1, rb), off, o);
-            }
+        if (prm.stream_out) {
+            store_cols<TOUT, 2 * QPL, kStoreStream>(r0, prm.w, px0, on, !ODD, e);
+            store_cols<TOUT, 2 * QPL, kStoreStream>(r1, prm.w, px0, on, !ODD, o);
         } else {
-#pragma unroll
-            for (int k = 0; k < 2 * QPL; ++k) {
-                if (px0 + k < prm.w) {
-                    r0[px0 + k] = from_float<TOUT>(e[k]);
-                    r1[px0 + k] = from_float<TOUT>(o[k]);
-                }
-            }
+            store_cols<TOUT, 2 * QPL>(r0, prm.w, px0, on, !ODD, e);
+            store_cols<TOUT, 2 * QPL>(r1, prm.w, px0, on, !ODD, o);
         }
     }
 }
 
-template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT>
+template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT,
+          bool ODD>
 __device__ __forceinline__ void inv_tile(const InvParams &prm, int t, Mailbox<QPL, WAVES> &box,
                                          int lane, int wave) {
     using G = TileGeom<WV, QPL, ROWS, WAVES>;
@@ -443,7 +380,7 @@ __device__ __forceinline__ void inv_tile(const InvParams &prm, int t, Mailbox<QP
     const float uLL = (float)(1.0 / (L::ZL * L::ZL)), uHL = (float)(1.0 / (L::ZL * L::ZH));
     const float uHH = (float)(1.0 / (L::ZH * L::ZH));
     Quads<ROWS, QPL> q;
-    inv_load<QPL, ROWS, G, TLL, TB>(q, prm, t, lane, wave);
+    inv_load<QPL, ROWS, G, TLL, TB, ODD>(q, prm, t, lane, wave);
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
 #pragma unroll
@@ -459,15 +396,16 @@ __device__ __forceinline__ void inv_tile(const InvParams &prm, int t, Mailbox<QP
         Exchange<ROWS, QPL, WAVES> x{&box, wave, lane, 0};
         lift_inverse<WV, SCH>(q, x);
     }
-    inv_store<QPL, ROWS, WAVES, G, TOUT>(q, prm, t, lane, wave);
+    inv_store<QPL, ROWS, WAVES, G, TOUT, ODD>(q, prm, t, lane, wave);
 }
 
-template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT>
+template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT,
+          bool ODD>
 __global__ __launch_bounds__(64 * WAVES) void inv_level_kernel(InvParams prm) {
     __shared__ Mailbox<QPL, WAVES> box;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform per wavefront
-    inv_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT>(prm, block_tile(), box, lane, wave);
+    inv_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT, ODD>(prm, block_tile(), box, lane, wave);
 }
 
 // ---- single levels of many images, parameters in the kernel arguments -----------
@@ -501,7 +439,8 @@ __device__ __forceinline__ int batch_image(const B &bt, int t) {
     return lo;
 }
 
-template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TIN, typename TLL, typename TB>
+template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TIN, typename TLL, typename TB,
+          bool ODD>
 __global__ __launch_bounds__(64 * WAVES) void fwd_batch_kernel(FwdBatch bt) {
     __shared__ Mailbox<QPL, WAVES> box;
     const int lane = threadIdx.x & 63;
@@ -509,12 +448,13 @@ __global__ __launch_bounds__(64 * WAVES) void fwd_batch_kernel(FwdBatch bt) {
     const int total = bt.tile_start[bt.n];
     for (int t = block_tile(); t < total; t += gridDim.x) {
         const int i = batch_image(bt, t);
-        fwd_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB>(bt.p[i], t - bt.tile_start[i], box, lane,
+        fwd_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB, ODD>(bt.p[i], t - bt.tile_start[i], box, lane,
                                                           wave);
     }
 }
 
-template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT>
+template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT,
+          bool ODD>
 __global__ __launch_bounds__(64 * WAVES) void inv_batch_kernel(InvBatch bt) {
     __shared__ Mailbox<QPL, WAVES> box;
     const int lane = threadIdx.x & 63;
@@ -522,7 +462,7 @@ __global__ __launch_bounds__(64 * WAVES) void inv_batch_kernel(InvBatch bt) {
     const int total = bt.tile_start[bt.n];
     for (int t = block_tile(); t < total; t += gridDim.x) {
         const int i = batch_image(bt, t);
-        inv_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT>(bt.p[i], t - bt.tile_start[i], box, lane,
+        inv_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT, ODD>(bt.p[i], t - bt.tile_start[i], box, lane,
                                                            wave);
     }
 }
@@ -544,7 +484,8 @@ struct TableLaunch {
 // Every workgroup walks the tiles t = its id, id + gridDim.x, ... below
 // `total`: one tile each when the grid has one workgroup per tile, several
 // when the grid is capped at the resident workgroups (persistent).
-template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TIN, typename TLL, typename TB>
+template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TIN, typename TLL, typename TB,
+          bool ODD>
 __global__ __launch_bounds__(64 * WAVES) void fwd_table_kernel(TableLaunch<FwdParams> tl) {
     __shared__ Mailbox<QPL, WAVES> box;
     const int lane = threadIdx.x & 63;
@@ -552,11 +493,12 @@ __global__ __launch_bounds__(64 * WAVES) void fwd_table_kernel(TableLaunch<FwdPa
     for (int t = block_tile(); t < tl.total; t += gridDim.x) {
         const int i = __builtin_amdgcn_readfirstlane(tl.img[t]);
         const FwdParams prm = tl.params[i];
-        fwd_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB>(prm, t - tl.start[i], box, lane, wave);
+        fwd_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB, ODD>(prm, t - tl.start[i], box, lane, wave);
     }
 }
 
-template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT>
+template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT,
+          bool ODD>
 __global__ __launch_bounds__(64 * WAVES) void inv_table_kernel(TableLaunch<InvParams> tl) {
     __shared__ Mailbox<QPL, WAVES> box;
     const int lane = threadIdx.x & 63;
@@ -564,7 +506,7 @@ __global__ __launch_bounds__(64 * WAVES) void inv_table_kernel(TableLaunch<InvPa
     for (int t = block_tile(); t < tl.total; t += gridDim.x) {
         const int i = __builtin_amdgcn_readfirstlane(tl.img[t]);
         const InvParams prm = tl.params[i];
-        inv_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT>(prm, t - tl.start[i], box, lane, wave);
+        inv_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT, ODD>(prm, t - tl.start[i], box, lane, wave);
     }
 }
 

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <array>
+#include <type_traits>
 #include <utility>
 
 #include "dwt2_kernels.hpp"
@@ -27,6 +28,16 @@ constexpr TileCfg kTiles[] = {
 };
 constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 
+// The kernel for rows at words, or for rows that may start at odd halves (2-byte
+// elements): make(integral_constant<bool>) gives either.
+template <typename T, typename Make>
+auto pick_kernel(bool odd, Make make) {
+    if constexpr (sizeof(T) == 2) {
+        if (odd) return make(std::true_type{});
+    }
+    return make(std::false_type{});
+}
+
 // A launcher takes the level parameters (grid fields filled in by the host
 // planner) and launches its kernel.
 using FwdLauncher = hipError_t (*)(const FwdParams &, hipStream_t);
@@ -35,16 +46,20 @@ using InvLauncher = hipError_t (*)(const InvParams &, hipStream_t);
 template <int WV, int SCH, int T, typename TIN, typename TLL, typename TB>
 hipError_t launch_fwd(const FwdParams &p, hipStream_t s) {
     constexpr TileCfg c = kTiles[T];
-    hipLaunchKernelGGL((fwd_level_kernel<WV, SCH, c.qpl, c.rows, c.waves, TIN, TLL, TB>),
-                       dim3(p.tiles_x * p.tiles_y), dim3(64 * c.waves), 0, s, p);
+    const auto k = pick_kernel<TB>(odd_rows(p), [](auto odd) {
+        return &fwd_level_kernel<WV, SCH, c.qpl, c.rows, c.waves, TIN, TLL, TB, odd.value>;
+    });
+    hipLaunchKernelGGL(k, dim3(p.tiles_x * p.tiles_y), dim3(64 * c.waves), 0, s, p);
     return hipGetLastError();
 }
 
 template <int WV, int SCH, int T, typename TLL, typename TB, typename TOUT>
 hipError_t launch_inv(const InvParams &p, hipStream_t s) {
     constexpr TileCfg c = kTiles[T];
-    hipLaunchKernelGGL((inv_level_kernel<WV, SCH, c.qpl, c.rows, c.waves, TLL, TB, TOUT>),
-                       dim3(p.tiles_x * p.tiles_y), dim3(64 * c.waves), 0, s, p);
+    const auto k = pick_kernel<TB>(odd_rows(p), [](auto odd) {
+        return &inv_level_kernel<WV, SCH, c.qpl, c.rows, c.waves, TLL, TB, TOUT, odd.value>;
+    });
+    hipLaunchKernelGGL(k, dim3(p.tiles_x * p.tiles_y), dim3(64 * c.waves), 0, s, p);
     return hipGetLastError();
 }
 
@@ -57,8 +72,12 @@ hipError_t launch_fwd_batch(const FwdBatch &b, hipStream_t s) {
     constexpr TileCfg c = kTiles[T];
     const int total = b.tile_start[b.n];
     if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL((fwd_batch_kernel<WV, SCH, c.qpl, c.rows, c.waves, TIN, TLL, TB>),
-                       dim3(total), dim3(64 * c.waves), 0, s, b);
+    bool any_odd = false;
+    for (int i = 0; i < b.n; ++i) any_odd |= odd_rows(b.p[i]);
+    const auto k = pick_kernel<TB>(any_odd, [](auto odd) {
+        return &fwd_batch_kernel<WV, SCH, c.qpl, c.rows, c.waves, TIN, TLL, TB, odd.value>;
+    });
+    hipLaunchKernelGGL(k, dim3(total), dim3(64 * c.waves), 0, s, b);
     return hipGetLastError();
 }
 
@@ -67,28 +86,41 @@ hipError_t launch_inv_batch(const InvBatch &b, hipStream_t s) {
     constexpr TileCfg c = kTiles[T];
     const int total = b.tile_start[b.n];
     if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL((inv_batch_kernel<WV, SCH, c.qpl, c.rows, c.waves, TLL, TB, TOUT>),
-                       dim3(total), dim3(64 * c.waves), 0, s, b);
+    bool any_odd = false;
+    for (int i = 0; i < b.n; ++i) any_odd |= odd_rows(b.p[i]);
+    const auto k = pick_kernel<TB>(any_odd, [](auto odd) {
+        return &inv_batch_kernel<WV, SCH, c.qpl, c.rows, c.waves, TLL, TB, TOUT, odd.value>;
+    });
+    hipLaunchKernelGGL(k, dim3(total), dim3(64 * c.waves), 0, s, b);
     return hipGetLastError();
 }
 
 // Workgroups of `kernel` that fit on the current device at once.
 int resident_blocks(const void *kernel, int block_threads);
 
-// Planned batches: one launch over a device table. `persistent` caps the grid
+// Planned batches: one launch over a device table. `any_odd`: odd_rows of any of
+// its images. `persistent` caps the grid
 // at the workgroups that fit on the device at once (each then walks several
 // tiles); otherwise the grid has one workgroup per tile.
-using FwdTableLauncher = hipError_t (*)(const TableLaunch<FwdParams> &, bool, hipStream_t);
-using InvTableLauncher = hipError_t (*)(const TableLaunch<InvParams> &, bool, hipStream_t);
+using FwdTableLauncher = hipError_t (*)(const TableLaunch<FwdParams> &, bool any_odd,
+                                        bool persistent, hipStream_t);
+using InvTableLauncher = hipError_t (*)(const TableLaunch<InvParams> &, bool any_odd,
+                                        bool persistent, hipStream_t);
 
 template <int WV, int SCH, int T, typename TIN, typename TLL, typename TB>
-hipError_t launch_fwd_table(const TableLaunch<FwdParams> &tl, bool persistent, hipStream_t s) {
+hipError_t launch_fwd_table(const TableLaunch<FwdParams> &tl, bool any_odd, bool persistent,
+                            hipStream_t s) {
     constexpr TileCfg c = kTiles[T];
-    const auto k = fwd_table_kernel<WV, SCH, c.qpl, c.rows, c.waves, TIN, TLL, TB>;
+    const auto kernel = [](auto odd) {
+        return &fwd_table_kernel<WV, SCH, c.qpl, c.rows, c.waves, TIN, TLL, TB, odd.value>;
+    };
+    const auto k = pick_kernel<TB>(any_odd, kernel);
     int grid = tl.total;
     if (persistent) {
-        static const int resident = resident_blocks((const void *)k, 64 * c.waves);
-        grid = grid < resident ? grid : resident;
+        static const int resident[2] = {
+            resident_blocks((const void *)pick_kernel<TB>(false, kernel), 64 * c.waves),
+            resident_blocks((const void *)pick_kernel<TB>(true, kernel), 64 * c.waves)};
+        grid = grid < resident[any_odd] ? grid : resident[any_odd];
     }
     if (grid <= 0) return hipSuccess;
     hipLaunchKernelGGL(k, dim3(grid), dim3(64 * c.waves), 0, s, tl);
@@ -96,13 +128,19 @@ hipError_t launch_fwd_table(const TableLaunch<FwdParams> &tl, bool persistent, h
 }
 
 template <int WV, int SCH, int T, typename TLL, typename TB, typename TOUT>
-hipError_t launch_inv_table(const TableLaunch<InvParams> &tl, bool persistent, hipStream_t s) {
+hipError_t launch_inv_table(const TableLaunch<InvParams> &tl, bool any_odd, bool persistent,
+                            hipStream_t s) {
     constexpr TileCfg c = kTiles[T];
-    const auto k = inv_table_kernel<WV, SCH, c.qpl, c.rows, c.waves, TLL, TB, TOUT>;
+    const auto kernel = [](auto odd) {
+        return &inv_table_kernel<WV, SCH, c.qpl, c.rows, c.waves, TLL, TB, TOUT, odd.value>;
+    };
+    const auto k = pick_kernel<TB>(any_odd, kernel);
     int grid = tl.total;
     if (persistent) {
-        static const int resident = resident_blocks((const void *)k, 64 * c.waves);
-        grid = grid < resident ? grid : resident;
+        static const int resident[2] = {
+            resident_blocks((const void *)pick_kernel<TB>(false, kernel), 64 * c.waves),
+            resident_blocks((const void *)pick_kernel<TB>(true, kernel), 64 * c.waves)};
+        grid = grid < resident[any_odd] ? grid : resident[any_odd];
     }
     if (grid <= 0) return hipSuccess;
     hipLaunchKernelGGL(k, dim3(grid), dim3(64 * c.waves), 0, s, tl);

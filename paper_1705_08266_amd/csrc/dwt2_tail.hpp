@@ -134,7 +134,14 @@ __global__ __launch_bounds__(64 * kTailWaves) void fwd_tail_kernel(FwdTail t) {
         }
         Quads<ROWS, QPL> q;
         if (m == 0) {
-            fwd_load_at<QPL, ROWS, TIN>(q, prm, qx, qy0);
+            bool done = false;
+            if constexpr (sizeof(TIN) == 2) {
+                if (!prm.vec_in) {
+                    fwd_load_at<QPL, ROWS, TIN, true>(q, prm, qx, qy0);
+                    done = true;
+                }
+            }
+            if (!done) fwd_load_at<QPL, ROWS, TIN, false>(q, prm, qx, qy0);
         } else {
             // the level input is the previous level's LL, held in LDS for its
             // computed region
@@ -210,7 +217,7 @@ __global__ __launch_bounds__(64 * kTailWaves) void inv_tail_kernel(InvTail t) {
         }
         Quads<ROWS, QPL> q;
         if (m == 0) {
-            inv_load_at<QPL, ROWS, TLL, TB>(q, prm, qx, qy0);
+            inv_load_at<QPL, ROWS, TLL, TB, false>(q, prm, qx, qy0);
         } else {
             // LL from the previous (coarser) level's output in LDS; the detail
             // bands from the pyramid. Each phase is extended on its own grid.
@@ -252,8 +259,7 @@ __global__ __launch_bounds__(64 * kTailWaves) void inv_tail_kernel(InvTail t) {
         lift_inverse<WV, SCH>(q, x);
         const bool last = m == F - 1;
         float *dst = pxbuf[m & 1];
-        const uint32_t oo = (qx >= g.ox0 && qx < g.ox1) ? 2u * (uint32_t)qx * sizeof(TOUT)
-                                                        : kNoAccess;
+        const bool own_x = qx >= g.ox0 && qx < g.ox1;
         const bool comp_x = qx >= g.cx0 && qx < g.cx1;
         int64_t ro = (int64_t)(2 * qy0) * prm.out_pitch;   // pixel row 2 gy
 #pragma unroll
@@ -261,19 +267,11 @@ __global__ __launch_bounds__(64 * kTailWaves) void inv_tail_kernel(InvTail t) {
             const int gy = qy0 + r;
             if (last) {
                 if (gy >= g.oy0 && gy < g.oy1) {   // wavefront-uniform
-                    const rsrc_t r0 = row_at<TOUT>(prm.out, ro, prm.w);
-                    const rsrc_t r1 = row_at<TOUT>(prm.out, ro + prm.out_pitch, prm.w);
-                    if (prm.vec_out) {
-                        const float e[2] = {q.a[r][0], q.b[r][0]};
-                        const float o[2] = {q.c[r][0], q.d[r][0]};
-                        store_vec<TOUT, 2>(r0, oo, e);
-                        store_vec<TOUT, 2>(r1, oo, o);
-                    } else {
-                        store_elem<TOUT>(r0, oo, q.a[r][0]);
-                        store_elem<TOUT>(r0, oo + (uint32_t)sizeof(TOUT), q.b[r][0]);
-                        store_elem<TOUT>(r1, oo, q.c[r][0]);
-                        store_elem<TOUT>(r1, oo + (uint32_t)sizeof(TOUT), q.d[r][0]);
-                    }
+                    const float e[2] = {q.a[r][0], q.b[r][0]};
+                    const float o[2] = {q.c[r][0], q.d[r][0]};
+                    const TOUT *r0 = static_cast<const TOUT *>(prm.out) + ro;
+                    store_cols<TOUT, 2>(r0, prm.w, 2 * qx, own_x, prm.vec_out, e);
+                    store_cols<TOUT, 2>(r0 + prm.out_pitch, prm.w, 2 * qx, own_x, prm.vec_out, o);
                 }
             } else if (comp_x && gy >= g.cy0 && gy < g.cy1) {
                 float *p0 = dst + (2 * (gy - g.cy0)) * cw + 2 * (qx - g.cx0);

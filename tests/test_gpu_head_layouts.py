@@ -22,8 +22,9 @@ def _cus():
 
 
 @pytest.mark.parametrize("wavelet,dtype,inverse,eighths",
-                         [("cdf97", torch.float32, False, 16), ("cdf97", torch.float16, False, 32),
+                         [("cdf97", torch.float32, False, 16), ("cdf97", torch.float16, False, 40),
                           ("cdf97", torch.float32, True, 16), ("cdf97", torch.bfloat16, True, 24),
+                          ("cdf97", torch.float16, True, 48),
                           ("cdf53", torch.float16, True, 3), ("cdf53", torch.bfloat16, True, 11)])
 def test_both_sides_of_the_line(wavelet, dtype, inverse, eighths):
     """Launches of exactly the windows of the line, and of one more."""
@@ -37,8 +38,8 @@ def test_both_sides_of_the_line(wavelet, dtype, inverse, eighths):
 
 
 def _thin(k):
-    """Windows of either direction beyond 4 per compute unit, and k pixels."""
-    return (4 * _cus() + 1) * 88 + k
+    """Windows of either direction beyond 6 per compute unit, and k pixels."""
+    return (6 * _cus() + 1) * 88 + k
 
 
 @pytest.mark.parametrize("width", [4, 192, 196, 584])
@@ -54,7 +55,7 @@ def test_strips_of_tall_images(dtype, pad, width):
 @pytest.mark.parametrize("dtype", DTYPES)
 def test_strips_of_wide_images(dtype, height):
     print(f"case wide {dtype} height {height}", flush=True)
-    w = (4 * _cus() + 1) * 58 * 4 + 4
+    w = (6 * _cus() + 1) * 58 * 4 + 4
     for pad in ((0,) if dtype == torch.float32 else (0, 7)):
         _both_ways(_crop(height, w, pad, dtype, 13), pad, "cdf97", "nonseparable")
 
@@ -85,3 +86,16 @@ def test_head_level_batch_by_strips(monkeypatch, inverse):
     torch.cuda.synchronize()
     for ra, rb in zip(a, b):
         assert torch.equal(ra[1], rb[1]), tuple(ra[0].shape)
+
+
+@pytest.mark.parametrize("pad", [0, 16, 7])
+def test_windows_of_rows_off_the_sectors(pad):
+    """FP32 forwards of more windows than the line, by windows where the band
+    rows are off the 64-byte sectors, else by strips."""
+    h, w = _thin(4), 128
+    print(f"case off sectors pad {pad}", flush=True)
+    x = _crop(h, w, pad, torch.float32, 14)
+    out = torch.full((h, w + pad), -7.0, device="cuda")
+    dwt.forward(x, "cdf97", 2, out=out[:, :w], tiles=HEAD)
+    assert torch.equal(dwt.forward(x, "cdf97", 2, tiles=[0, 0]), out[:, :w])
+    assert bool((out[:, w:] == -7).all())
