@@ -18,6 +18,8 @@
 #include <hip/hip_fp16.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 // A product and a sum are never fused unless fmaf says so: the same lifting
 // inlined into different kernels has to round alike.
 #pragma clang fp contract(off)
@@ -72,6 +74,23 @@ template <> struct Storage<bf16_t> {
     static constexpr int code = DT_BF16;
     __device__ static float decode(uint32_t v) { return __uint_as_float(v << 16); }
 };
+
+// Headroom of the lifting. Its steps add up to four neighbours before they
+// multiply, and such a sum may exceed FLT_MAX where every value of the transform
+// is in range (a 5/3 image of 1.8e38, 9/7 stripes of 2e37). So values are
+// scaled by 2^-2 on the way in and back on the way out, and a step overflows only
+// where its result does. A power of two changes no bit of a result beyond
+// 2^-124. Halves end at 65504, whose sums are far from the limit: where nothing
+// but halves comes in, or goes out, the factor is 1. Elsewhere a forward
+// multiplies its pixels and an inverse its results once more; the factors at
+// the other end are there already. Between fused levels the low-low band stays
+// scaled: one that exceeds FLT_MAX itself is infinite only where it is stored.
+template <typename... T>
+constexpr bool kAllHalf = (std::is_same<T, __half>::value && ...);
+template <typename TIN>
+constexpr float kFwdHeadroom = kAllHalf<TIN> ? 1.0f : 0.25f;
+template <typename TLL, typename TB, typename TOUT>
+constexpr float kInvHeadroom = kAllHalf<TOUT> || kAllHalf<TLL, TB> ? 1.0f : 0.25f;
 
 __device__ __forceinline__ float to_float(float v) { return v; }
 __device__ __forceinline__ float to_float(__half v) { return __half2float(v); }
@@ -451,9 +470,13 @@ struct Exchange {
 // stays symmetric to the last bit, and a kernel may either carry the extension
 // along as halo quads or put a quad's own value in a missing neighbour's
 // place (p (x + x) at the right and lower edge, u (y + y) at the left and
-// upper) and get the same result. The sums also round less: the 5-level
-// forward error against 64 bits is 4.5e-6 of the 2-norm (5.0e-6 with one FMA
-// per tap), the round trip 3.2e-6 of 255 (3.9e-6).
+// upper) and get the same result. Against 64 bits, relative 2-norm, one level
+// of 1024^2 in FP32 (with one FMA per tap): 9/7 forward 3.7e-7 (4.7e-7), inverse
+// 3.0e-7 (3.5e-7); 5/3 inverse of a smooth picture 4.3e-8 (4.9e-8), but its
+// forward 6.2e-8 (5.6e-8): there the sum of two neighbours rounds at the pixels'
+// magnitude, not at the detail's. 8-bit pictures are exact in 5/3. T_P's d takes
+// the c pair and the b pair one after the other (one sum of four: 9/7 3.8e-7,
+// 5/3 7.1e-8), S_U's a takes one sum (two: 3.8e-7, 6.7e-8).
 template <int QPL>
 __device__ __forceinline__ void add_right(const float (&x)[QPL], float (&s)[QPL]) {
     const float xr = from_right(x[0]);
@@ -487,7 +510,7 @@ __device__ __forceinline__ void nonsep_predict(Quads<ROWS, QPL> &q, Exchange<ROW
         for (int i = 0; i < QPL; ++i) {
             const float ad = (r + 1 < ROWS) ? q.a[(r + 1 < ROWS) ? r + 1 : r][i] : na[i];
             const float bd = (r + 1 < ROWS) ? q.b[(r + 1 < ROWS) ? r + 1 : r][i] : nb[i];
-            q.d[r][i] = fmaf(p, s[i] + (q.b[r][i] + bd), q.d[r][i]);
+            q.d[r][i] = fmaf(p, q.b[r][i] + bd, fmaf(p, s[i], q.d[r][i]));
             q.c[r][i] = fmaf(p, q.a[r][i] + ad, q.c[r][i]);
         }
     }
@@ -652,7 +675,7 @@ __device__ __forceinline__ void nonsep_predict_lds(Quads<ROWS, QPL> &q,
             const float bd = (r + 1 < ROWS) ? q.b[(r + 1 < ROWS) ? r + 1 : r][i] : nb[i];
             const float c = q.c[r][i];
             const float cr = (i + 1 < QPL) ? q.c[r][(i + 1 < QPL) ? i + 1 : i] : cR[r];
-            q.d[r][i] = fmaf(p, (c + cr) + (q.b[r][i] + bd), q.d[r][i]);
+            q.d[r][i] = fmaf(p, q.b[r][i] + bd, fmaf(p, c + cr, q.d[r][i]));
             q.c[r][i] = fmaf(p, q.a[r][i] + ad, c);
         }
     }

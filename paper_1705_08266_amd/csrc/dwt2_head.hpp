@@ -88,14 +88,17 @@ __device__ __forceinline__ void fwd_head_strip(const FwdHead &hd, const int wx, 
     using G = HeadGeom<WV, OWN>;
     using L = Wavelet<WV>;
     constexpr int NP = G::NP, D = kHeadDepth;
-    // 4-byte pixels stay in the registers of their load until the next row has
-    // been lifted; 2-byte ones are decoded into others at once, and their
-    // registers can take the next load a row pair earlier
+    // 4-byte pixels stay in the registers of their load until their row is
+    // lifted (122 registers, not 94, if both rows are scaled first); 2-byte
+    // ones are decoded into others at once, and their registers can take the
+    // next load a row pair earlier
     constexpr bool KEEP = sizeof(TIN) == 4;
     constexpr int AHEAD = KEEP ? D - 1 : D;
     constexpr int POLICY = STREAM ? kStoreStream : kStoreCached;
-    const float sLL = (float)(L::ZL * L::ZL), sHL = (float)(L::ZL * L::ZH);
-    const float sHH = (float)(L::ZH * L::ZH);
+    constexpr float down = kFwdHeadroom<TIN>, up = 1.0f / down;
+    const float sLL = (float)(L::ZL * L::ZL) * up, sHL = (float)(L::ZL * L::ZH) * up;
+    const float sHH = (float)(L::ZH * L::ZH) * up;
+    const float sL1 = (float)(L::ZL * L::ZL);             // between the levels
     const FwdParams &p1 = hd.l1, &p2 = hd.l2;
     const int lane = threadIdx.x & 63;
     const int X = wx + lane;                              // the lane's level j+1 column
@@ -119,8 +122,8 @@ __device__ __forceinline__ void fwd_head_strip(const FwdHead &hd, const int wx, 
     const RowsOf<TLL, MODE> ll2(p2.ll, p2.ll_pitch, p2.nqy, p2.nqx, t0 - 1 - NP);
     uint32_t s_in = 0, s_b1 = 0, s_b2 = 0, s_ll = 0;      // row offsets, stepped
 
-    FwdRows<WV, SCH, 2, EX, EY, KEEP> v1{};
-    FwdRows<WV, SCH, 1, EX, EY, false> v2{};
+    FwdRows<WV, SCH, 2, EX, EY> v1{};
+    FwdRows<WV, SCH, 1, EX, EY> v2{};
     Raw<TIN, 4, MODE> raw[D][4];
     const auto fetch = [&](int t, Raw<TIN, 4, MODE>(&w)[4]) {
         const uint32_t off = t <= t1 ? offi : kNoAccess;
@@ -142,20 +145,25 @@ __device__ __forceinline__ void fwd_head_strip(const FwdHead &hd, const int wx, 
             const int t = tb + i;
             __builtin_amdgcn_s_barrier();                 // lockstep
             Line<2> x[2];
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
+            const auto take = [&](int k) {
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
-                    x[k].a[j] = raw[i][2 * k].get(2 * j);
-                    x[k].b[j] = raw[i][2 * k].get(2 * j + 1);
-                    x[k].c[j] = raw[i][2 * k + 1].get(2 * j);
-                    x[k].d[j] = raw[i][2 * k + 1].get(2 * j + 1);
+                    x[k].a[j] = raw[i][2 * k].get(2 * j) * down;
+                    x[k].b[j] = raw[i][2 * k].get(2 * j + 1) * down;
+                    x[k].c[j] = raw[i][2 * k + 1].get(2 * j) * down;
+                    x[k].d[j] = raw[i][2 * k + 1].get(2 * j + 1) * down;
                 }
-            if constexpr (!KEEP) fetch(t + D, raw[i]);
+            };
+            if constexpr (!KEEP) {
+                take(0);
+                take(1);
+                fetch(t + D, raw[i]);
+            }
             __builtin_amdgcn_sched_barrier(0);
             const uint32_t o1 = (t - 1 >= o && t - 1 < e) ? off1 : kNoAccess;
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
+                if constexpr (KEEP) take(k);
                 v1.push(x[k], 2 * t + NP - 2 + k, p1.nqy, m);
                 const float vb[2] = {x[k].b[0] * sHL, x[k].b[1] * sHL};
                 const float vc[2] = {x[k].c[0] * sHL, x[k].c[1] * sHL};
@@ -172,8 +180,8 @@ __device__ __forceinline__ void fwd_head_strip(const FwdHead &hd, const int wx, 
                 }
             }
             Line<1> q;
-            q.a[0] = x[0].a[0] * sLL; q.b[0] = x[0].a[1] * sLL;
-            q.c[0] = x[1].a[0] * sLL; q.d[0] = x[1].a[1] * sLL;
+            q.a[0] = x[0].a[0] * sL1; q.b[0] = x[0].a[1] * sL1;
+            q.c[0] = x[1].a[0] * sL1; q.d[0] = x[1].a[1] * sL1;
             v2.push(q, t - 1, p2.nqy, m);
             const int y = t - 1 - NP;
             const bool on = y >= o && y < e;
@@ -202,8 +210,11 @@ __device__ __forceinline__ void inv_head_strip(const InvHead &hd, const int wx, 
     using L = Wavelet<WV>;
     constexpr int NP = G::NP, D = kHeadDepth;
     constexpr int POLICY = STREAM ? kStoreStream : kStoreCached;
-    const float uLL = (float)(1.0 / (L::ZL * L::ZL)), uHL = (float)(1.0 / (L::ZL * L::ZH));
-    const float uHH = (float)(1.0 / (L::ZH * L::ZH));
+    constexpr float down = kInvHeadroom<TLL, TB, TOUT>, up = 1.0f / down;
+    const float uLL = (float)(1.0 / (L::ZL * L::ZL)) * down;
+    const float uHL = (float)(1.0 / (L::ZL * L::ZH)) * down;
+    const float uHH = (float)(1.0 / (L::ZH * L::ZH)) * down;
+    const float uL1 = (float)(1.0 / (L::ZL * L::ZL));     // between the levels
     const InvParams &p1 = hd.l1, &p2 = hd.l2;
     const int lane = threadIdx.x & 63;
     const int X = wx + lane;
@@ -279,17 +290,20 @@ __device__ __forceinline__ void inv_head_strip(const InvHead &hd, const int wx, 
             fetch(t + D, raw[i]);
             __builtin_amdgcn_sched_barrier(0);
             v2.push(q, t, p2.nqy, m);
-            x[0].a[0] = q.a[0] * uLL; x[0].a[1] = q.b[0] * uLL;
-            x[1].a[0] = q.c[0] * uLL; x[1].a[1] = q.d[0] * uLL;
+            x[0].a[0] = q.a[0] * uL1; x[0].a[1] = q.b[0] * uL1;
+            x[1].a[0] = q.c[0] * uL1; x[1].a[1] = q.d[0] * uL1;
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 v1.push(x[k], 2 * (t - NP) + k, p1.nqy, m);
                 const int y = 2 * (t - NP) - NP + k;
                 const uint32_t oo = (y >= 2 * o && y < 2 * e) ? offo : kNoAccess;
-                const float ev[4] = {x[k].a[0], x[k].b[0], x[k].a[1], x[k].b[1]};
-                const float od[4] = {x[k].c[0], x[k].d[0], x[k].c[1], x[k].d[1]};
+                const float ev[4] = {x[k].a[0] * up, x[k].b[0] * up, x[k].a[1] * up, x[k].b[1] * up};
                 out.template store<4, POLICY>(2 * y, oo, s_o, ev);
                 s_o += out.step;
+                // one pixel row's registers at a time: 114 in the FP32 9/7 kernel
+                // instead of 130, which would leave three wavefronts to a SIMD
+                __builtin_amdgcn_sched_barrier(0);
+                const float od[4] = {x[k].c[0] * up, x[k].d[0] * up, x[k].c[1] * up, x[k].d[1] * up};
                 out.template store<4, POLICY>(2 * y + 1, oo, s_o, od);
                 s_o += out.step;
             }

@@ -108,8 +108,10 @@ __device__ __forceinline__ void fwd_head_tile(const FwdHead &hd, const int t,
     constexpr int RG = G::RG, H2 = G::FH2, R2 = G::FROWS2, NR1 = G::NR1;
     Mailbox<2, WAVES> &box = lds.box;
     float(&ll1)[4][H2][64] = lds.ll1;
-    const float sLL = (float)(L::ZL * L::ZL), sHL = (float)(L::ZL * L::ZH);
-    const float sHH = (float)(L::ZH * L::ZH);
+    constexpr float up = 1.0f / kFwdHeadroom<TIN>;
+    const float sLL = (float)(L::ZL * L::ZL) * up, sHL = (float)(L::ZL * L::ZH) * up;
+    const float sHH = (float)(L::ZH * L::ZH) * up;
+    const float sL1 = (float)(L::ZL * L::ZL);           // between the levels
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ty = t / hd.across, tx = t - ty * hd.across;
@@ -133,8 +135,8 @@ __device__ __forceinline__ void fwd_head_tile(const FwdHead &hd, const int t,
                 const int rr = wave * ROWS + r - RG;
                 if (rr >= 0 && rr < 2 * H2) {
                     const int ph = 2 * (rr & 1);
-                    ll1[ph][rr >> 1][lane - 1] = q.a[r][0] * sLL;
-                    ll1[ph + 1][rr >> 1][lane - 1] = q.a[r][1] * sLL;
+                    ll1[ph][rr >> 1][lane - 1] = q.a[r][0] * sL1;
+                    ll1[ph + 1][rr >> 1][lane - 1] = q.a[r][1] * sL1;
                 }
             }
         }
@@ -226,8 +228,11 @@ __device__ __forceinline__ void inv_head_tile(const InvHead &hd, const int t,
     constexpr int RG = G::RG, H2 = G::IH2, R2 = G::IROWS2, NR1 = G::NR1;
     Mailbox<2, WAVES> &box = lds.box;     // level j+1 exchanges (smaller), then level j's
     float(&ll1)[4][H2][64] = lds.ll1;     // level j low-low as level j+1 output quads
-    const float uLL = (float)(1.0 / (L::ZL * L::ZL)), uHL = (float)(1.0 / (L::ZL * L::ZH));
-    const float uHH = (float)(1.0 / (L::ZH * L::ZH));
+    constexpr float down = kInvHeadroom<TLL, TB, TOUT>, up = 1.0f / down;
+    const float uLL = (float)(1.0 / (L::ZL * L::ZL)) * down;
+    const float uHL = (float)(1.0 / (L::ZL * L::ZH)) * down;
+    const float uHH = (float)(1.0 / (L::ZH * L::ZH)) * down;
+    const float uL1 = (float)(1.0 / (L::ZL * L::ZL));    // between the levels
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ty = t / hd.across, tx = t - ty * hd.across;
@@ -303,7 +308,7 @@ __device__ __forceinline__ void inv_head_tile(const InvHead &hd, const int t,
     for (int r = 0; r < ROWS; ++r) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            q.a[r][i] *= uLL; q.b[r][i] *= uHL; q.c[r][i] *= uHL; q.d[r][i] *= uHH;
+            q.a[r][i] *= uL1; q.b[r][i] *= uHL; q.c[r][i] *= uHL; q.d[r][i] *= uHH;
         }
     }
     {
@@ -320,8 +325,8 @@ __device__ __forceinline__ void inv_head_tile(const InvHead &hd, const int t,
         const int wr = wave * ROWS + r;
         const int gy = qy0 + r;
         if (wr < RG || wr >= RG + G::IOY1 || gy >= p1.nqy) continue;   // wavefront-uniform
-        const float e[4] = {q.a[r][0], q.b[r][0], q.a[r][1], q.b[r][1]};
-        const float o[4] = {q.c[r][0], q.d[r][0], q.c[r][1], q.d[r][1]};
+        const float e[4] = {q.a[r][0] * up, q.b[r][0] * up, q.a[r][1] * up, q.b[r][1] * up};
+        const float o[4] = {q.c[r][0] * up, q.d[r][0] * up, q.c[r][1] * up, q.d[r][1] * up};
         TOUT *r0p = out + ro;
         TOUT *r1p = r0p + p1.out_pitch;
         if (p1.stream_out) {

@@ -147,10 +147,12 @@ __device__ __forceinline__ void fix_cols(const RowIn<T, E, ODD> (&rows)[N], cons
 
 // The lane's quads start at quad column qx0 and quad row qy0 of the level;
 // positions outside the level are read through the symmetric extension.
-// ODD: rows may start at the upper half of a word (2-byte elements).
+// ODD: rows may start at the upper half of a word (2-byte elements). The values
+// are scaled by kFwdHeadroom<TIN>.
 template <int QPL, int ROWS, typename TIN, bool ODD>
 __device__ __forceinline__ void fwd_load_at(Quads<ROWS, QPL> &q, const FwdParams &prm, int qx0,
                                             int qy0) {
+    constexpr float down = kFwdHeadroom<TIN>;
     const TIN *in = static_cast<const TIN *>(prm.in);
     const int px0 = 2 * qx0;
     int m[2 * QPL];
@@ -184,8 +186,8 @@ __device__ __forceinline__ void fwd_load_at(Quads<ROWS, QPL> &q, const FwdParams
     for (int r = 0; r < ROWS; ++r) {
 #pragma unroll
         for (int i = 0; i < QPL; ++i) {
-            q.a[r][i] = v[2 * r][2 * i]; q.b[r][i] = v[2 * r][2 * i + 1];
-            q.c[r][i] = v[2 * r + 1][2 * i]; q.d[r][i] = v[2 * r + 1][2 * i + 1];
+            q.a[r][i] = v[2 * r][2 * i] * down; q.b[r][i] = v[2 * r][2 * i + 1] * down;
+            q.c[r][i] = v[2 * r + 1][2 * i] * down; q.d[r][i] = v[2 * r + 1][2 * i + 1] * down;
         }
     }
 }
@@ -197,12 +199,14 @@ __device__ __forceinline__ void fwd_load(Quads<ROWS, QPL> &q, const FwdParams &p
                                      ty * G::OY - G::HY + wave * ROWS);
 }
 
-template <int WV, int QPL, int ROWS, int WAVES, typename G, typename TLL, typename TB, bool ODD>
+template <int WV, int QPL, int ROWS, int WAVES, typename G, typename TIN, typename TLL, typename TB,
+          bool ODD>
 __device__ __forceinline__ void fwd_store(const Quads<ROWS, QPL> &q, const FwdParams &prm, int t,
                                           int lane, int wave) {
     using L = Wavelet<WV>;
-    const float sLL = (float)(L::ZL * L::ZL), sHL = (float)(L::ZL * L::ZH);
-    const float sHH = (float)(L::ZH * L::ZH);
+    constexpr float up = 1.0f / kFwdHeadroom<TIN>;
+    const float sLL = (float)(L::ZL * L::ZL) * up, sHL = (float)(L::ZL * L::ZH) * up;
+    const float sHH = (float)(L::ZH * L::ZH) * up;
     if (lane == 0 || lane == 63) return;   // halo lanes
     const int ty = t / prm.tiles_x, tx = t - (t / prm.tiles_x) * prm.tiles_x;
     const int qx0 = tx * G::OX - G::HX + lane * QPL;
@@ -249,7 +253,7 @@ __device__ __forceinline__ void fwd_tile(const FwdParams &prm, int t, Mailbox<QP
         Exchange<ROWS, QPL, WAVES> x{&box, wave, lane, 0};
         lift_forward<WV, SCH>(q, x);
     }
-    fwd_store<WV, QPL, ROWS, WAVES, G, TLL, TB, ODD>(q, prm, t, lane, wave);
+    fwd_store<WV, QPL, ROWS, WAVES, G, TIN, TLL, TB, ODD>(q, prm, t, lane, wave);
 }
 
 // One tile per workgroup.
@@ -337,9 +341,10 @@ __device__ __forceinline__ void inv_load(Quads<ROWS, QPL> &q, const InvParams &p
                                          ty * G::OY - G::HY + wave * ROWS);
 }
 
+// up: what the values are multiplied by on their way out.
 template <int QPL, int ROWS, int WAVES, typename G, typename TOUT, bool ODD>
 __device__ __forceinline__ void inv_store(const Quads<ROWS, QPL> &q, const InvParams &prm, int t,
-                                          int lane, int wave) {
+                                          int lane, int wave, float up) {
     if (lane == 0 || lane == 63) return;   // halo lanes
     const int ty = t / prm.tiles_x, tx = t - (t / prm.tiles_x) * prm.tiles_x;
     const int qx0 = tx * G::OX - G::HX + lane * QPL;
@@ -356,8 +361,8 @@ __device__ __forceinline__ void inv_store(const Quads<ROWS, QPL> &q, const InvPa
         float e[2 * QPL], o[2 * QPL];
 #pragma unroll
         for (int i = 0; i < QPL; ++i) {
-            e[2 * i] = q.a[r][i]; e[2 * i + 1] = q.b[r][i];
-            o[2 * i] = q.c[r][i]; o[2 * i + 1] = q.d[r][i];
+            e[2 * i] = q.a[r][i] * up; e[2 * i + 1] = q.b[r][i] * up;
+            o[2 * i] = q.c[r][i] * up; o[2 * i + 1] = q.d[r][i] * up;
         }
         TOUT *r0 = out + ro;
         TOUT *r1 = r0 + prm.out_pitch;
@@ -377,8 +382,10 @@ __device__ __forceinline__ void inv_tile(const InvParams &prm, int t, Mailbox<QP
                                          int lane, int wave) {
     using G = TileGeom<WV, QPL, ROWS, WAVES>;
     using L = Wavelet<WV>;
-    const float uLL = (float)(1.0 / (L::ZL * L::ZL)), uHL = (float)(1.0 / (L::ZL * L::ZH));
-    const float uHH = (float)(1.0 / (L::ZH * L::ZH));
+    constexpr float down = kInvHeadroom<TLL, TB, TOUT>;
+    const float uLL = (float)(1.0 / (L::ZL * L::ZL)) * down;
+    const float uHL = (float)(1.0 / (L::ZL * L::ZH)) * down;
+    const float uHH = (float)(1.0 / (L::ZH * L::ZH)) * down;
     Quads<ROWS, QPL> q;
     inv_load<QPL, ROWS, G, TLL, TB, ODD>(q, prm, t, lane, wave);
 #pragma unroll
@@ -396,7 +403,7 @@ __device__ __forceinline__ void inv_tile(const InvParams &prm, int t, Mailbox<QP
         Exchange<ROWS, QPL, WAVES> x{&box, wave, lane, 0};
         lift_inverse<WV, SCH>(q, x);
     }
-    inv_store<QPL, ROWS, WAVES, G, TOUT, ODD>(q, prm, t, lane, wave);
+    inv_store<QPL, ROWS, WAVES, G, TOUT, ODD>(q, prm, t, lane, wave, 1.0f / down);
 }
 
 template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT,

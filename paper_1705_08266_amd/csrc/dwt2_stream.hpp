@@ -233,26 +233,10 @@ __device__ __forceinline__ void sum_left(const float (&x)[QPL], float (&s)[QPL],
     for (int i = 0; i < QPL; ++i) s[i] = x[i] + ((i > 0) ? x[(i > 0) ? i - 1 : i] : xl);
 }
 
-// fmaf(a, b, c) into a register of its own (NEW): the compiler's two-address
-// FMA would update c in place, and a value that has just been loaded would
-// then sit in the register of its load through the whole pipeline, so that the
-// load of a later row needs copies, and a wait, at the end of the row loop.
-template <bool NEW>
-__device__ __forceinline__ float fma_to(float a, float b, float c) {
-    if constexpr (NEW) {
-        float r;
-        asm("v_fma_f32 %0, %1, %2, %3" : "=v"(r) : "s"(a), "v"(b), "v"(c));
-        return r;
-    } else {
-        return fmaf(a, b, c);
-    }
-}
-
-// One forward lifting pair (T_P, then S_U). LOADED: the rows come straight
-// from memory.
+// One forward lifting pair (T_P, then S_U).
 //   push(x, bottom, top): x is row r; emits row r - 1 in x. bottom (top): row
 //   r - 1 is the level's last (first) row.
-template <int SCH, int QPL, bool EX, bool EY, bool LOADED>
+template <int SCH, int QPL, bool EX, bool EY>
 struct FwdStage {
     Line<QPL> y;                // the waiting row: b after T_P (separable: d after T_P^H too)
     float pc[QPL], pd[QPL];     // of the row above y: what S_U^V adds
@@ -266,8 +250,8 @@ struct FwdStage {
         if constexpr (SCH != NONSEP) sum_right<EX>(x.c, sc, m);
 #pragma unroll
         for (int i = 0; i < QPL; ++i) {
-            x.b[i] = fma_to<LOADED>(p, s[i], x.b[i]);
-            if constexpr (SCH != NONSEP) x.d[i] = fma_to<LOADED>(p, sc[i], x.d[i]);
+            x.b[i] = fmaf(p, s[i], x.b[i]);
+            if constexpr (SCH != NONSEP) x.d[i] = fmaf(p, sc[i], x.d[i]);
         }
         // row r - 1: the rest of T_P
         if constexpr (SCH == NONSEP) sum_right<EX>(z.c, sc, m);
@@ -279,8 +263,8 @@ struct FwdStage {
                 xa = bottom ? z.a[i] : xa;
                 xb = bottom ? z.b[i] : xb;
             }
-            c[i] = fma_to<LOADED>(p, z.a[i] + xa, z.c[i]);
-            if constexpr (SCH == NONSEP) z.d[i] = fma_to<LOADED>(p, sc[i] + (z.b[i] + xb), z.d[i]);
+            c[i] = fmaf(p, z.a[i] + xa, z.c[i]);
+            if constexpr (SCH == NONSEP) z.d[i] = fmaf(p, z.b[i] + xb, fmaf(p, sc[i], z.d[i]));
             else z.d[i] = fmaf(p, z.b[i] + xb, z.d[i]);
         }
         // row r - 1: S_U
@@ -298,7 +282,7 @@ struct FwdStage {
             sum_left<EX>(z.b, sb, m);
 #pragma unroll
             for (int i = 0; i < QPL; ++i) {
-                z.a[i] = fma_to<LOADED>(u, sb[i] + (c[i] + pc[i]), z.a[i]);
+                z.a[i] = fmaf(u, sb[i] + (c[i] + pc[i]), z.a[i]);
                 z.c[i] = fmaf(u, sd[i], c[i]);
                 pc[i] = c[i];
                 pd[i] = z.d[i];
@@ -309,7 +293,7 @@ struct FwdStage {
             sum_left<EX>(z.d, sd, m);
 #pragma unroll
             for (int i = 0; i < QPL; ++i) {
-                z.a[i] = fma_to<LOADED>(u, sb[i], z.a[i]);
+                z.a[i] = fmaf(u, sb[i], z.a[i]);
                 z.c[i] = fmaf(u, sd[i], c[i]);
                 if constexpr (EY) {
                     pc[i] = top ? z.c[i] : pc[i];
@@ -388,7 +372,7 @@ struct InvStage {
                 xa = bottom ? z.a[i] : xa;
                 xb = bottom ? z.b[i] : xb;
             }
-            if constexpr (SCH == NONSEP) z.d[i] = fmaf(p, sc[i] + (z.b[i] + xb), z.d[i]);
+            if constexpr (SCH == NONSEP) z.d[i] = fmaf(p, z.b[i] + xb, fmaf(p, sc[i], z.d[i]));
             else z.d[i] = fmaf(p, z.b[i] + xb, z.d[i]);
             z.c[i] = fmaf(p, z.a[i] + xa, z.c[i]);
         }
@@ -408,11 +392,11 @@ struct InvStage {
 
 // All lifting pairs of one level. push(x, r, n): x is row r of n; emits row
 // r - NPAIRS.
-template <int WV, int SCH, int QPL, bool EX, bool EY, bool LOADED>
+template <int WV, int SCH, int QPL, bool EX, bool EY>
 struct FwdRows {
     static constexpr int NP = Wavelet<WV>::NPAIRS;
-    FwdStage<SCH, QPL, EX, EY, LOADED> s0;
-    FwdStage<SCH, QPL, EX, EY, false> s1;   // 9/7 only
+    FwdStage<SCH, QPL, EX, EY> s0;
+    FwdStage<SCH, QPL, EX, EY> s1;   // 9/7 only
     __device__ __forceinline__ void push(Line<QPL> &x, int r, int n, ColMarks m) {
         using L = Wavelet<WV>;
         s0.push(x, (float)L::p(0), (float)L::u(0), m, r - 1 == n - 1, r - 1 == 0);

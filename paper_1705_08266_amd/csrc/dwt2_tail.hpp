@@ -116,8 +116,10 @@ __global__ __launch_bounds__(64 * kTailWaves) void fwd_tail_kernel(FwdTail t) {
     // pyramids overlap, run on the same XCD and share its L2
     const int blk = block_tile();
     const int bx = blk % t.blocks_x, by = blk / t.blocks_x;
-    const float sLL = (float)(L::ZL * L::ZL), sHL = (float)(L::ZL * L::ZH);
-    const float sHH = (float)(L::ZH * L::ZH);
+    constexpr float up = 1.0f / kFwdHeadroom<TIN>;
+    const float sLL = (float)(L::ZL * L::ZL) * up, sHL = (float)(L::ZL * L::ZH) * up;
+    const float sHH = (float)(L::ZH * L::ZH) * up;
+    const float sL1 = (float)(L::ZL * L::ZL);   // between the levels
     int px0 = 0, py0 = 0, pw = 1, ph = 1;       // previous level's LL region in LDS
 #pragma unroll
     for (int m = 0; m < F; ++m) {
@@ -170,7 +172,7 @@ __global__ __launch_bounds__(64 * kTailWaves) void fwd_tail_kernel(FwdTail t) {
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
             const int gy = qy0 + r;
-            const float va = q.a[r][0] * sLL;
+            const float va = q.a[r][0] * (last ? sLL : sL1);
             if (gy >= g.oy0 && gy < g.oy1) {   // wavefront-uniform
                 store_elem<TB>(row_at<TB>(prm.hl, rb, prm.nqx), ob, q.b[r][0] * sHL);
                 store_elem<TB>(row_at<TB>(prm.lh, rb, prm.nqx), ob, q.c[r][0] * sHL);
@@ -199,8 +201,11 @@ __global__ __launch_bounds__(64 * kTailWaves) void inv_tail_kernel(InvTail t) {
     // pyramids overlap, run on the same XCD and share its L2
     const int blk = block_tile();
     const int bx = blk % t.blocks_x, by = blk / t.blocks_x;
-    const float uLL = (float)(1.0 / (L::ZL * L::ZL)), uHL = (float)(1.0 / (L::ZL * L::ZH));
-    const float uHH = (float)(1.0 / (L::ZH * L::ZH));
+    constexpr float down = kInvHeadroom<TLL, TB, TOUT>, up = 1.0f / down;
+    const float uLL = (float)(1.0 / (L::ZL * L::ZL)) * down;
+    const float uHL = (float)(1.0 / (L::ZL * L::ZH)) * down;
+    const float uHH = (float)(1.0 / (L::ZH * L::ZH)) * down;
+    const float uL1 = (float)(1.0 / (L::ZL * L::ZL));   // between the levels
     int px0 = 0, py0 = 0, pw = 1, ph = 1;       // previous level's output region in LDS
 #pragma unroll
     for (int m = 0; m < F; ++m) {
@@ -253,7 +258,8 @@ __global__ __launch_bounds__(64 * kTailWaves) void inv_tail_kernel(InvTail t) {
         }
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            q.a[r][0] *= uLL; q.b[r][0] *= uHL; q.c[r][0] *= uHL; q.d[r][0] *= uHH;
+            q.a[r][0] *= m == 0 ? uLL : uL1;
+            q.b[r][0] *= uHL; q.c[r][0] *= uHL; q.d[r][0] *= uHH;
         }
         Exchange<ROWS, QPL, WAVES> x{&box, wave, lane, 0};
         lift_inverse<WV, SCH>(q, x);
@@ -267,8 +273,8 @@ __global__ __launch_bounds__(64 * kTailWaves) void inv_tail_kernel(InvTail t) {
             const int gy = qy0 + r;
             if (last) {
                 if (gy >= g.oy0 && gy < g.oy1) {   // wavefront-uniform
-                    const float e[2] = {q.a[r][0], q.b[r][0]};
-                    const float o[2] = {q.c[r][0], q.d[r][0]};
+                    const float e[2] = {q.a[r][0] * up, q.b[r][0] * up};
+                    const float o[2] = {q.c[r][0] * up, q.d[r][0] * up};
                     const TOUT *r0 = static_cast<const TOUT *>(prm.out) + ro;
                     store_cols<TOUT, 2>(r0, prm.w, 2 * qx, own_x, prm.vec_out, e);
                     store_cols<TOUT, 2>(r0 + prm.out_pitch, prm.w, 2 * qx, own_x, prm.vec_out, o);
