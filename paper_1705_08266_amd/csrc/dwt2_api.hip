@@ -315,10 +315,12 @@ TailPlan plan_inv_tail(int F, int wavelet, int nqx_first, int nqy_first) {
 // compute units, and evenly: once the memory is busy every CU gets an equal
 // share of it, so a CU with one workgroup more than the others ends that much
 // later (4096^2 FP32 forward: 31.6 us with 237 workgroups on 256 CUs, 40.8
-// with 270). So for c = 1..4 workgroups per CU the smallest segment whose grid
-// has at most c per CU is weighed, at the time its row pairs take: measured
-// 0.97, 1.8, 2.85, 3.5 us each with c = 1, 2, 3, 4 workgroups on a CU in FP32,
-// 0.83, 1.23, 1.75, 2.3 with 16-bit storage, whatever the image (FP32 with
+// with 270). So for c = 1..8 workgroups per CU the smallest segment whose grid
+// has at most c per CU, if there is one (a launch of many small images has more
+// strips than that at any height), is weighed at the time its row pairs take:
+// measured 0.97, 1.8, 2.85, 3.5 us each with c = 1, 2, 3, 4 workgroups on a CU
+// in FP32, 0.83, 1.23, 1.75, 2.3 with 16-bit storage, whatever the image, and
+// beyond four, which is what fits on a CU, in proportion (FP32 with
 // streamed output 1.7 at c = 2: 5504^2 inverse 53.0 us against 57.9 at c = 1). Forward, us
 // with c = 1, 2, 3, 4: FP32 2048^2 12.8, 14.6 and 7680x4320 56.1, 60.0, 62.5,
 // 63.3; 16-bit 2048^2 12.5, 13.4, 4096^2 27.7, 25.1, 27.7 and 7680x4320 47.5,
@@ -346,18 +348,20 @@ int head_segment(const HeadShape *im, int n, int wavelet, bool wide, bool invers
     int tallest = 1;
     for (int i = 0; i < n; ++i) tallest = std::max(tallest, im[i].nqy);
     double best = 0;
-    int seg = tallest;
-    for (int c = 1; c <= 4; ++c) {
+    int seg = many;
+    for (int c = 1; c <= 8; ++c) {
         int lo = 1, hi = tallest;   // smallest segment with at most c workgroups per CU
         while (lo < hi) {
             const int mid = (lo + hi) / 2;
             if (head_tasks(im, n, mid) <= c * kHeadWaves * cus) hi = mid; else lo = mid + 1;
         }
+        if (head_tasks(im, n, lo) > c * kHeadWaves * cus) continue;   // none has
         const int pairs = (lo + halo + D - 1) / D * D;   // whole groups of D
-        const double cost =
-            pairs * (wide && streamed && c == 2 ? kPairTimeStream2 : kPairTime[wide][c - 1]);
-        if (best == 0 || cost < best) {
-            best = cost;
+        const double time = c > 4 ? kPairTime[wide][3] * c / 4
+                            : wide && streamed && c == 2 ? kPairTimeStream2
+                                                         : kPairTime[wide][c - 1];
+        if (best == 0 || pairs * time < best) {
+            best = pairs * time;
             seg = std::min(pairs - halo, tallest);
         }
     }

@@ -1,0 +1,59 @@
+"""The rows per segment that a planned head launch gives its strips, read from
+plans built on the host. A strip walks the rows of its segment and a few more,
+so a launch of many images takes at least (segment + halo) row pairs per strip:
+one tall image among thousands of small ones must not make theirs tall."""
+import ctypes
+import struct
+
+import pytest
+
+from paper_1705_08266_amd import _lib
+
+from test_batch_plan_host import FAKE, HEADER, LAUNCH
+
+# sizeof of the launch's parameters per image; the segment is their last field
+PARAMS = {0: 216, 1: 200}
+OWN, HALO = 48, 6
+
+
+def _head(sizes, dtype, wavelet, inverse):
+    """(segment, row pairs that a launch with it walks, and with 18) of a plan."""
+    lib = _lib.load()
+    es = 4 if dtype == _lib.F32 else 2
+    arr = (_lib.Image * len(sizes))()
+    base = FAKE
+    for i, (w, h) in enumerate(sizes):
+        ws = lib.dwt2_workspace_bytes(w, h, 2, dtype)
+        arr[i] = _lib.Image(base, w, base + w * h * es, w, base + 2 * w * h * es, ws, w, h)
+        base += 2 * w * h * es + ws + 4096
+    n = ctypes.c_size_t()
+    args = (arr, len(sizes), dtype, wavelet, 2, inverse, 0, None, _lib.PLAN_HEAD)
+    assert lib.dwt2_batch_plan_bytes(*args, ctypes.byref(n)) == 0
+    buf = (ctypes.c_ubyte * n.value)()
+    assert lib.dwt2_batch_plan(*args, buf, n.value) == 0
+    launches = HEADER.unpack_from(buf)[7]
+    assert launches == 1
+    off = LAUNCH.unpack_from(buf, HEADER.size)[8]
+    seg = struct.unpack_from("<i", buf, off + PARAMS[inverse] - 4)[0]
+
+    def pairs(rows):
+        return sum(-(-(w // 4) // OWN) * -(-(h // 4) // rows) * (rows + HALO) for w, h in sizes)
+
+    return seg, pairs(seg) if seg else 0, pairs(18)
+
+
+@pytest.mark.parametrize("inverse", [0, 1])
+@pytest.mark.parametrize("dtype", [_lib.F32, _lib.F16, _lib.BF16])
+@pytest.mark.parametrize("small,count", [(64, 4000), (64, 5000), (32, 6000), (128, 2500)])
+def test_one_tall_image_among_small_ones(dtype, inverse, small, count):
+    """At most twice the row pairs of segments of 18 rows."""
+    seg, walked, short = _head([(small, small)] * count + [(4096, 4096)], dtype, 0, inverse)
+    assert seg > 0 and walked <= 2 * short, (seg, walked, short)
+
+
+@pytest.mark.parametrize("inverse", [0, 1])
+@pytest.mark.parametrize("dtype", [_lib.F32, _lib.F16])
+def test_small_images_alone(dtype, inverse):
+    for count in (1100, 4200, 8000):
+        seg, walked, short = _head([(32, 32)] * count, dtype, 0, inverse)
+        assert seg == 8 or seg == 0, seg     # no taller than the images
