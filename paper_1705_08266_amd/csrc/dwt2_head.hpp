@@ -103,7 +103,7 @@ __device__ __forceinline__ void fwd_head_strip(const FwdHead &hd, const int wx, 
     const int lane = threadIdx.x & 63;
     const int X = wx + lane;                              // the lane's level j+1 column
     const int e = min(o + hd.seg, p2.nqy);
-    const int t0 = o - G::F0, t1 = e + G::F1, tl = o + hd.seg + G::F1;
+    const int t0 = o - G::F0, t1 = e + G::F1;
     const ColMarks m{X == 0, X == p2.nqx - 1};
     const bool own = lane >= G::HALO && lane < G::HALO + OWN && X < p2.nqx;
     const uint32_t offi = 4u * (uint32_t)min(max(X, 0), p2.nqx - 1) * (uint32_t)sizeof(TIN);
@@ -139,7 +139,7 @@ __device__ __forceinline__ void fwd_head_strip(const FwdHead &hd, const int wx, 
         fetch(t0 + i, raw[i]);
         pad_stores((KEEP && i + 1 == AHEAD) ? 7 : 10);
     }
-    for (int tb = t0; tb <= tl; tb += D) {
+    for (int tb = t0; tb <= t1; tb += D) {
 #pragma unroll
         for (int i = 0; i < D; ++i) {
             const int t = tb + i;
@@ -219,7 +219,7 @@ __device__ __forceinline__ void inv_head_strip(const InvHead &hd, const int wx, 
     const int lane = threadIdx.x & 63;
     const int X = wx + lane;
     const int e = min(o + hd.seg, p2.nqy);
-    const int t0 = o - G::I0, t1 = e + G::I1, tl = o + hd.seg + G::I1;
+    const int t0 = o - G::I0, t1 = e + G::I1;
     const ColMarks m{X == 0, X == p2.nqx - 1};
     const bool own = lane >= G::HALO && lane < G::HALO + OWN && X < p2.nqx;
     const uint32_t Xc = (uint32_t)min(max(X, 0), p2.nqx - 1);
@@ -269,7 +269,7 @@ __device__ __forceinline__ void inv_head_strip(const InvHead &hd, const int wx, 
         fetch(t0 + i, raw[i]);
         pad_stores(4);
     }
-    for (int tb = t0; tb <= tl; tb += D) {
+    for (int tb = t0; tb <= t1; tb += D) {
 #pragma unroll
         for (int i = 0; i < D; ++i) {
             const int t = tb + i;
@@ -318,9 +318,10 @@ __device__ __forceinline__ bool within_span(int64_t rows, int64_t pitch) {
     return rows * pitch * (int64_t)sizeof(T) < (int64_t)(kSpan / 2);
 }
 
-// Task `task` of a head: strip by strip along x, then segment by segment. The
-// wavefronts of a workgroup run it on tasks of equal segment height, so that
-// they pass the same barriers.
+// Task `task` of a head: strip by strip along x, then segment by segment. A
+// sweep ends with its own segment, cut off at the image's end or not: the
+// barriers of the others then wait for one wavefront less, and as they guard
+// no data, a wavefront that goes on to its next task may pass them out of step.
 template <int WV, int SCH, int OWN, typename TIN, typename TLL, typename TB, bool STREAM>
 __device__ __forceinline__ void fwd_head_task(const FwdHead &hd, const int task) {
     using G = HeadGeom<WV, OWN>;
