@@ -400,29 +400,40 @@ int64_t head_windows(const HeadShape &im, bool inverse) {
 // of lines at every piece end, and lose to windows again where those are many:
 // pitch of 28 bytes more, 1026 windows: 35.6, 34.4; 1848: 58.3, 61.7; 4104: 112.9,
 // 123.3; 15848 x 16384: 445, 462 (16384^2, on lines: 474, 403).
-bool head_by_windows(const HeadShape *im, int n, int wavelet, bool wide, bool inverse,
+// 2-byte rows that may start at odd halves: the strips' shifted loads and split
+// stores stand in the serial chain of each row pair, the windows' between loads
+// that are all in flight, and windows last longer. Rows of 7 elements more:
+//   9/7 forward 24 windows: 9.6, 12.9 (9.3, 12.5); 602: 18.1, 21.4 (21.9, 22.9);
+//     1548: 31.8, 37.2 (38.7, 40.4); 4104: 69.5, 72.9 (86.6, 79.5)
+//   9/7 inverse 18: 9.5, 13.4 (9.3, 13.1); 1260: 30.9, 37.8 (39.2, 41.6); 3384: 71.2,
+//     74.3 (98.2, 90.9)
+//   5/3 forward 261: 10.8, 14.9 (12.7, 15.8); 602: 16.2, 18.0 (19.9, 20.2); 798: 20.0,
+//     18.3 (23.5, 21.7)
+//   5/3 inverse 490: 13.4, 19.3 (16.3, 21.6); 846: 21.6, 22.8 (26.4, 27.6); 1260: 28.5,
+//     28.2 (36.5, 36.1)
+bool head_by_windows(const HeadShape *im, int n, int wavelet, bool wide, bool inverse, bool odd,
                      bool streamed, bool off_sectors) {
     const int64_t cus = device_cus();
     int64_t w = 0;
     for (int i = 0; i < n; ++i) w += head_windows(im[i], inverse);
+    if (odd) return 2 * w <= cus * (wavelet == DWT2_CDF97 ? 16 : inverse ? 8 : 5);
     if (wavelet == DWT2_CDF97 && wide && !inverse && off_sectors && w > 6 * cus) return true;
     if (wavelet == DWT2_CDF97) return w <= cus * (wide ? 2 : !inverse ? 5 : streamed ? 6 : 3);
     return inverse && !wide && 8 * w > 3 * cus && 8 * w <= 11 * cus;
 }
-// Whether pixel or level j band rows of a head may start at odd halves of a word.
-bool head_odd(const FwdHead &h) { return !(h.l1.vec_in && h.l1.vec_band); }
-bool head_odd(const InvHead &h) { return !(h.l1.vec_band && h.l1.vec_out); }
 // Whether level j band rows start off the 64-byte sectors (forward).
 bool head_off_sectors(const FwdHead &h) {
     const size_t pitch = (size_t)h.l1.band_pitch * 4;   // looked at for FP32 only
     return (((uintptr_t)h.l1.hl | (uintptr_t)h.l1.lh | (uintptr_t)h.l1.hh | pitch) & 63) != 0;
 }
 bool head_off_sectors(const InvHead &) { return false; }
-// The rows per segment of a head launch, or 0 where it runs by windows, which
-// take rows at words only. odd: head_odd of any of the launch's images.
+// The rows per segment of a head launch, or 0 where it runs by windows. odd:
+// odd_rows of any of the launch's images (all of them then run the kernel for
+// such rows: 32 FP16 images of sides up to 4096, one level, 26.8 us forward with
+// one odd image among them as without).
 int head_layout(const HeadShape *im, int n, int wavelet, bool wide, bool inverse, bool odd,
                 bool streamed = false, bool off_sectors = false) {
-    return !odd && head_by_windows(im, n, wavelet, wide, inverse, streamed, off_sectors)
+    return head_by_windows(im, n, wavelet, wide, inverse, odd, streamed, off_sectors)
                ? 0 : head_segment(im, n, wavelet, wide, inverse, streamed);
 }
 
@@ -439,7 +450,7 @@ int head_grid(H &hd, int seg) {
 template <typename H>
 int head_grid_one(H &hd, int wavelet, int dt, bool inverse, bool streamed) {
     const HeadShape im{hd.l2.nqx, hd.l2.nqy};
-    return head_grid(hd, head_layout(&im, 1, wavelet, dt == DWT2_F32, inverse, head_odd(hd),
+    return head_grid(hd, head_layout(&im, 1, wavelet, dt == DWT2_F32, inverse, odd_rows(hd),
                                      streamed, head_off_sectors(hd)));
 }
 
@@ -665,7 +676,7 @@ const PlanLaunch *plan_launches(const PlanHeader *h) {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// odd_rows of any image of a level launch (plan: its host copy).
+// odd_rows of any image of a launch (plan: its host copy).
 template <typename P>
 bool any_odd_rows(const void *plan, const PlanLaunch &l) {
     const P *p = reinterpret_cast<const P *>(static_cast<const char *>(plan) + l.off_params);
@@ -803,7 +814,7 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
                                    cb + (size_t)((int64_t)(H / 2) * cp) * es,
                                    cb + (size_t)((int64_t)(H / 2) * cp + W / 2) * es, cp, dtype,
                                    im.dst, im.dst_pitch, dtype, W, H, wavelet, 0);
-                odd |= head_odd(hd);
+                odd |= odd_rows(hd);
                 G.ih.push_back(hd);
             } else {
                 char *cb = static_cast<char *>(im.dst);
@@ -819,7 +830,7 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
                                    cb + (size_t)((int64_t)(H / 4) * cp) * es,
                                    cb + (size_t)((int64_t)(H / 4) * cp + W / 4) * es, cp, dtype,
                                    wavelet, 0);
-                odd |= head_odd(hd);
+                odd |= odd_rows(hd);
                 G.fh.push_back(hd);
             }
         }
@@ -1355,12 +1366,12 @@ int dwt2_batch_run(const void *plan, size_t plan_bytes, const void *plan_device,
                 const TableLaunch<InvHead> tl{img, start, reinterpret_cast<const InvHead *>(prm),
                                               tasks};
                 e = inv_head_plan_table(h->dtype)[h->wavelet][scheme][l.f32_a][l.f32_b](
-                    tl, windows, persistent, stream);
+                    tl, windows, any_odd_rows<InvHead>(plan, l), persistent, stream);
             } else {
                 const TableLaunch<FwdHead> tl{img, start, reinterpret_cast<const FwdHead *>(prm),
                                               tasks};
                 e = fwd_head_plan_table(h->dtype)[h->wavelet][scheme][l.f32_a][l.f32_b](
-                    tl, windows, persistent, stream);
+                    tl, windows, any_odd_rows<FwdHead>(plan, l), persistent, stream);
             }
         } else if (h->inverse) {
             TableLaunch<InvParams> tl{reinterpret_cast<const int32_t *>(dev + l.off_img),
@@ -1576,7 +1587,7 @@ int head_batch(const dwt2_level_job *jobs, int32_t n, int32_t wavelet, int32_t s
                 // one layout and segment height for the launch: its workgroups
                 // hold strips of several images
                 bool odd = false;
-                for (int k = 0; k < b.n; ++k) odd |= head_odd(b.h[k]);
+                for (int k = 0; k < b.n; ++k) odd |= odd_rows(b.h[k]);
                 const int seg =
                     head_layout(shapes, b.n, wavelet, key.band_dt == DWT2_F32, INV, odd);
                 if (seg && head_tasks(shapes, b.n, seg) > (int64_t)INT32_MAX - kHeadWaves) {

@@ -42,8 +42,8 @@
 
 namespace dwt2 {
 
-// 12 wavefronts of 4 quad rows. Every row starts at a word (2-byte rows at odd
-// halves go by strips).
+// 12 wavefronts of 4 quad rows. Rows that may start at odd halves have kernels of
+// their own, as in the one-level launches.
 constexpr int kHeadTileRows = 4, kHeadTileWaves = 12;
 
 template <int ROWS, int WAVES>
@@ -97,10 +97,11 @@ using FwdTileLds = TileLds<WAVES, WindowGeom<ROWS, WAVES>::FH2>;
 template <int ROWS, int WAVES>
 using InvTileLds = TileLds<WAVES, WindowGeom<ROWS, WAVES>::IH2>;
 
-// Levels j and j+1 of forward head tile t (row-major over tiles_x x tiles_y).
+// Levels j and j+1 of forward window t (row-major, hd.across to a row). ODD:
+// rows may start at the upper half of a word (2-byte elements).
 // Wavefronts below the coarser level's window return early, after passing its
 // barriers.
-template <int WV, int SCH, int ROWS, int WAVES, typename TIN, typename TLL, typename TB>
+template <int WV, int SCH, int ROWS, int WAVES, typename TIN, typename TLL, typename TB, bool ODD>
 __device__ __forceinline__ void fwd_head_tile(const FwdHead &hd, const int t,
                                               FwdTileLds<ROWS, WAVES> &lds) {
     using G = WindowGeom<ROWS, WAVES>;
@@ -123,7 +124,7 @@ __device__ __forceinline__ void fwd_head_tile(const FwdHead &hd, const int t,
         const int qx = 2 * (ox2 - RG - 1 + lane);       // the lane's first quad column
         const int qy0 = 2 * oy2 - 3 * RG + wave * ROWS; // its first quad row
         Quads<ROWS, 2> q;
-        fwd_load_at<2, ROWS, TIN, false>(q, p1, qx, qy0);
+        fwd_load_at<2, ROWS, TIN, ODD>(q, p1, qx, qy0);
         {
             Exchange<ROWS, 2, WAVES> x{&box, wave, lane, 0};
             lift_forward<WV, SCH>(q, x);
@@ -157,9 +158,9 @@ __device__ __forceinline__ void fwd_head_tile(const FwdHead &hd, const int t,
             const float vb[2] = {q.b[r][0] * sHL, q.b[r][1] * sHL};
             const float vc[2] = {q.c[r][0] * sHL, q.c[r][1] * sHL};
             const float vd[2] = {q.d[r][0] * sHH, q.d[r][1] * sHH};
-            store_cols<TB, 2>(hl + rowo, p1.nqx, qx, own_x, true, vb);
-            store_cols<TB, 2>(lh + rowo, p1.nqx, qx, own_x, true, vc);
-            store_cols<TB, 2>(hh + rowo, p1.nqx, qx, own_x, true, vd);
+            store_cols<TB, 2>(hl + rowo, p1.nqx, qx, own_x, !ODD, vb);
+            store_cols<TB, 2>(lh + rowo, p1.nqx, qx, own_x, !ODD, vc);
+            store_cols<TB, 2>(hh + rowo, p1.nqx, qx, own_x, !ODD, vd);
         }
     }
 
@@ -219,8 +220,8 @@ __device__ __forceinline__ void fwd_head_tile(const FwdHead &hd, const int t,
     }
 }
 
-// Levels j+1 and j of inverse head tile t (row-major over tiles_x x tiles_y).
-template <int WV, int SCH, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT>
+// Levels j+1 and j of inverse window t (row-major, hd.across to a row).
+template <int WV, int SCH, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT, bool ODD>
 __device__ __forceinline__ void inv_head_tile(const InvHead &hd, const int t,
                                               InvTileLds<ROWS, WAVES> &lds) {
     using G = WindowGeom<ROWS, WAVES>;
@@ -272,7 +273,7 @@ __device__ __forceinline__ void inv_head_tile(const InvHead &hd, const int t,
     const int qx = wx1 + 2 * lane;
     const int qy0 = wy1 + wave * ROWS;
     Quads<ROWS, 2> q;
-    inv_load_at<2, ROWS, TB, TB, false, false>(q, p1, qx, qy0);
+    inv_load_at<2, ROWS, TB, TB, ODD, false>(q, p1, qx, qy0);
     {
         // the low-low coefficient of quad (i, j) is the extended low phase
         int cx[2], px[2];
@@ -330,27 +331,27 @@ __device__ __forceinline__ void inv_head_tile(const InvHead &hd, const int t,
         TOUT *r0p = out + ro;
         TOUT *r1p = r0p + p1.out_pitch;
         if (p1.stream_out) {
-            store_cols<TOUT, 4, kStoreStream>(r0p, p1.w, px0, on, true, e);
-            store_cols<TOUT, 4, kStoreStream>(r1p, p1.w, px0, on, true, o);
+            store_cols<TOUT, 4, kStoreStream>(r0p, p1.w, px0, on, !ODD, e);
+            store_cols<TOUT, 4, kStoreStream>(r1p, p1.w, px0, on, !ODD, o);
         } else {
-            store_cols<TOUT, 4>(r0p, p1.w, px0, on, true, e);
-            store_cols<TOUT, 4>(r1p, p1.w, px0, on, true, o);
+            store_cols<TOUT, 4>(r0p, p1.w, px0, on, !ODD, e);
+            store_cols<TOUT, 4>(r1p, p1.w, px0, on, !ODD, o);
         }
     }
 }
 
 // One workgroup per tile of one image.
-template <int WV, int SCH, int ROWS, int WAVES, typename TIN, typename TLL, typename TB>
+template <int WV, int SCH, int ROWS, int WAVES, typename TIN, typename TLL, typename TB, bool ODD>
 __global__ __launch_bounds__(64 * WAVES, (kFwdHeadWavesPerSimd<SCH, WAVES, TIN>)) void fwd_head_tile_kernel(
     FwdHead hd) {
     __shared__ FwdTileLds<ROWS, WAVES> lds;
-    fwd_head_tile<WV, SCH, ROWS, WAVES, TIN, TLL, TB>(hd, block_tile(), lds);
+    fwd_head_tile<WV, SCH, ROWS, WAVES, TIN, TLL, TB, ODD>(hd, block_tile(), lds);
 }
 
-template <int WV, int SCH, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT>
+template <int WV, int SCH, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT, bool ODD>
 __global__ __launch_bounds__(64 * WAVES, kInvHeadWavesPerSimd<WAVES>) void inv_head_tile_kernel(InvHead hd) {
     __shared__ InvTileLds<ROWS, WAVES> lds;
-    inv_head_tile<WV, SCH, ROWS, WAVES, TLL, TB, TOUT>(hd, block_tile(), lds);
+    inv_head_tile<WV, SCH, ROWS, WAVES, TLL, TB, TOUT, ODD>(hd, block_tile(), lds);
 }
 
 // Heads of a planned batch: the tiles of every image in one launch, each
@@ -358,47 +359,47 @@ __global__ __launch_bounds__(64 * WAVES, kInvHeadWavesPerSimd<WAVES>) void inv_h
 // tiles t = its id, id + gridDim.x, ... below `total` (several when the grid is
 // capped at the resident workgroups), with a barrier between tiles, which
 // share the LDS.
-template <int WV, int SCH, int ROWS, int WAVES, typename TIN, typename TLL, typename TB>
+template <int WV, int SCH, int ROWS, int WAVES, typename TIN, typename TLL, typename TB, bool ODD>
 __global__ __launch_bounds__(64 * WAVES, kTableHeadWavesPerSimd<WAVES>) void fwd_head_tile_table_kernel(
     TableLaunch<FwdHead> tl) {
     __shared__ FwdTileLds<ROWS, WAVES> lds;
     for (int t = block_tile(); t < tl.total; t += gridDim.x) {
         const int i = __builtin_amdgcn_readfirstlane(tl.img[t]);
         const FwdHead hd = tl.params[i];
-        fwd_head_tile<WV, SCH, ROWS, WAVES, TIN, TLL, TB>(hd, t - tl.start[i], lds);
+        fwd_head_tile<WV, SCH, ROWS, WAVES, TIN, TLL, TB, ODD>(hd, t - tl.start[i], lds);
         __syncthreads();
     }
 }
 
-template <int WV, int SCH, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT>
+template <int WV, int SCH, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT, bool ODD>
 __global__ __launch_bounds__(64 * WAVES, kTableHeadWavesPerSimd<WAVES>) void inv_head_tile_table_kernel(
     TableLaunch<InvHead> tl) {
     __shared__ InvTileLds<ROWS, WAVES> lds;
     for (int t = block_tile(); t < tl.total; t += gridDim.x) {
         const int i = __builtin_amdgcn_readfirstlane(tl.img[t]);
         const InvHead hd = tl.params[i];
-        inv_head_tile<WV, SCH, ROWS, WAVES, TLL, TB, TOUT>(hd, t - tl.start[i], lds);
+        inv_head_tile<WV, SCH, ROWS, WAVES, TLL, TB, TOUT, ODD>(hd, t - tl.start[i], lds);
         __syncthreads();
     }
 }
 
 // Heads of independent images in one launch, one workgroup per tile.
-template <int WV, int SCH, int ROWS, int WAVES, typename TIN, typename TLL, typename TB>
+template <int WV, int SCH, int ROWS, int WAVES, typename TIN, typename TLL, typename TB, bool ODD>
 __global__ __launch_bounds__(64 * WAVES, kTableHeadWavesPerSimd<WAVES>) void fwd_head_tile_batch_kernel(
     FwdHeadBatch bt) {
     __shared__ FwdTileLds<ROWS, WAVES> lds;
     const int t = block_tile();
     const int i = batch_image(bt, t);
-    fwd_head_tile<WV, SCH, ROWS, WAVES, TIN, TLL, TB>(bt.h[i], t - bt.tile_start[i], lds);
+    fwd_head_tile<WV, SCH, ROWS, WAVES, TIN, TLL, TB, ODD>(bt.h[i], t - bt.tile_start[i], lds);
 }
 
-template <int WV, int SCH, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT>
+template <int WV, int SCH, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT, bool ODD>
 __global__ __launch_bounds__(64 * WAVES, kTableHeadWavesPerSimd<WAVES>) void inv_head_tile_batch_kernel(
     InvHeadBatch bt) {
     __shared__ InvTileLds<ROWS, WAVES> lds;
     const int t = block_tile();
     const int i = batch_image(bt, t);
-    inv_head_tile<WV, SCH, ROWS, WAVES, TLL, TB, TOUT>(bt.h[i], t - bt.tile_start[i], lds);
+    inv_head_tile<WV, SCH, ROWS, WAVES, TLL, TB, TOUT, ODD>(bt.h[i], t - bt.tile_start[i], lds);
 }
 
 }  // namespace dwt2

@@ -318,18 +318,27 @@ using InvHeadLauncher = hipError_t (*)(const InvHead &, int tasks, bool stream, 
 inline int head_blocks(int tasks) { return (tasks + kHeadWaves - 1) / kHeadWaves; }
 
 using HeadWindow = WindowGeom<kHeadTileRows, kHeadTileWaves>;
-// Whether a head may run by windows: the 5/3 forward is faster by strips at
-// every size (FP32 and FP16, 1024^2: 7.7 us by windows, 6.0 by strips; 4096^2:
-// 34.9 and 30.6, 23.6 and 20.8).
-template <int WV>
-constexpr bool kFwdByWindows = WV == CDF97;
+// Whether a forward may run by windows: with 5/3 only the launches whose rows may
+// start at odd halves of a word; the others are faster by strips at every size
+// (FP32 and FP16, 1024^2: 7.7 us by windows, 6.0 by strips; 4096^2: 34.9 and
+// 30.6, 23.6 and 20.8).
+template <int WV, typename T>
+constexpr bool kFwdByWindows = WV == CDF97 || sizeof(T) == 2;
+template <int WV, typename T, typename Make>
+auto pick_fwd_window(bool odd, Make make) {
+    if constexpr (WV == CDF97) return pick_kernel<T>(odd, make);
+    else return make(std::true_type{});
+}
 
 template <int WV, int SCH, typename TIN, typename TLL, typename T>
 hipError_t launch_fwd_head(const FwdHead &h, int tasks, bool stream, hipStream_t s) {
-    if constexpr (kFwdByWindows<WV>) {
+    if constexpr (kFwdByWindows<WV, T>) {
         if (h.seg == 0) {
-            hipLaunchKernelGGL((fwd_head_tile_kernel<WV, SCH, kHeadTileRows, kHeadTileWaves, TIN, TLL, T>),
-                               dim3(tasks), dim3(64 * kHeadTileWaves), 0, s, h);
+            const auto k = pick_fwd_window<WV, T>(odd_rows(h), [](auto odd) {
+                return &fwd_head_tile_kernel<WV, SCH, kHeadTileRows, kHeadTileWaves, TIN, TLL, T,
+                                             odd.value>;
+            });
+            hipLaunchKernelGGL(k, dim3(tasks), dim3(64 * kHeadTileWaves), 0, s, h);
             return hipGetLastError();
         }
     }
@@ -343,8 +352,11 @@ hipError_t launch_fwd_head(const FwdHead &h, int tasks, bool stream, hipStream_t
 template <int WV, int SCH, typename TLL, typename T, typename TOUT>
 hipError_t launch_inv_head(const InvHead &h, int tasks, bool stream, hipStream_t s) {
     if (h.seg == 0) {
-        hipLaunchKernelGGL((inv_head_tile_kernel<WV, SCH, kHeadTileRows, kHeadTileWaves, TLL, T, TOUT>),
-                           dim3(tasks), dim3(64 * kHeadTileWaves), 0, s, h);
+        const auto k = pick_kernel<T>(odd_rows(h), [](auto odd) {
+            return &inv_head_tile_kernel<WV, SCH, kHeadTileRows, kHeadTileWaves, TLL, T, TOUT,
+                                         odd.value>;
+        });
+        hipLaunchKernelGGL(k, dim3(tasks), dim3(64 * kHeadTileWaves), 0, s, h);
         return hipGetLastError();
     }
     const dim3 grid(head_blocks(tasks)), block(64 * kHeadWaves);
@@ -380,23 +392,32 @@ constexpr InvHeadTable make_inv_head_table() {
 }
 
 // Heads of a planned batch: one launch over the windows or strips of every
-// image, indexed as the single-image head tables. `persistent` caps the grid at the
-// workgroups that fit on the device at once.
+// image, indexed as the single-image head tables. `any_odd`: odd_rows of any of
+// its images. `persistent` caps the grid at the workgroups that fit on the
+// device at once.
 using FwdHeadTableLauncher = hipError_t (*)(const TableLaunch<FwdHead> &, bool windows,
-                                            bool persistent, hipStream_t);
+                                            bool any_odd, bool persistent, hipStream_t);
 using InvHeadTableLauncher = hipError_t (*)(const TableLaunch<InvHead> &, bool windows,
-                                            bool persistent, hipStream_t);
+                                            bool any_odd, bool persistent, hipStream_t);
 
 template <int WV, int SCH, typename TIN, typename TLL, typename T>
-hipError_t launch_fwd_head_table(const TableLaunch<FwdHead> &tl, bool windows, bool persistent,
-                                 hipStream_t s) {
-    if constexpr (kFwdByWindows<WV>) {
+hipError_t launch_fwd_head_table(const TableLaunch<FwdHead> &tl, bool windows, bool any_odd,
+                                 bool persistent, hipStream_t s) {
+    if constexpr (kFwdByWindows<WV, T>) {
         if (windows) {
-            const auto k = fwd_head_tile_table_kernel<WV, SCH, kHeadTileRows, kHeadTileWaves, TIN, TLL, T>;
+            const auto kernel = [](auto odd) {
+                return &fwd_head_tile_table_kernel<WV, SCH, kHeadTileRows, kHeadTileWaves, TIN, TLL,
+                                                   T, odd.value>;
+            };
+            const auto k = pick_fwd_window<WV, T>(any_odd, kernel);
             int grid = tl.total;
             if (persistent) {
-                static const int resident = resident_blocks((const void *)k, 64 * kHeadTileWaves);
-                grid = grid < resident ? grid : resident;
+                static const int resident[2] = {
+                    resident_blocks((const void *)pick_fwd_window<WV, T>(false, kernel),
+                                    64 * kHeadTileWaves),
+                    resident_blocks((const void *)pick_fwd_window<WV, T>(true, kernel),
+                                    64 * kHeadTileWaves)};
+                grid = grid < resident[any_odd] ? grid : resident[any_odd];
             }
             if (grid <= 0) return hipSuccess;
             hipLaunchKernelGGL(k, dim3(grid), dim3(64 * kHeadTileWaves), 0, s, tl);
@@ -414,14 +435,20 @@ hipError_t launch_fwd_head_table(const TableLaunch<FwdHead> &tl, bool windows, b
     return hipGetLastError();
 }
 template <int WV, int SCH, typename TLL, typename T, typename TOUT>
-hipError_t launch_inv_head_table(const TableLaunch<InvHead> &tl, bool windows, bool persistent,
-                                 hipStream_t s) {
+hipError_t launch_inv_head_table(const TableLaunch<InvHead> &tl, bool windows, bool any_odd,
+                                 bool persistent, hipStream_t s) {
     if (windows) {
-        const auto k = inv_head_tile_table_kernel<WV, SCH, kHeadTileRows, kHeadTileWaves, TLL, T, TOUT>;
+        const auto kernel = [](auto odd) {
+            return &inv_head_tile_table_kernel<WV, SCH, kHeadTileRows, kHeadTileWaves, TLL, T, TOUT,
+                                               odd.value>;
+        };
+        const auto k = pick_kernel<T>(any_odd, kernel);
         int grid = tl.total;
         if (persistent) {
-            static const int resident = resident_blocks((const void *)k, 64 * kHeadTileWaves);
-            grid = grid < resident ? grid : resident;
+            static const int resident[2] = {
+                resident_blocks((const void *)pick_kernel<T>(false, kernel), 64 * kHeadTileWaves),
+                resident_blocks((const void *)pick_kernel<T>(true, kernel), 64 * kHeadTileWaves)};
+            grid = grid < resident[any_odd] ? grid : resident[any_odd];
         }
         if (grid <= 0) return hipSuccess;
         hipLaunchKernelGGL(k, dim3(grid), dim3(64 * kHeadTileWaves), 0, s, tl);
@@ -471,11 +498,16 @@ using InvHeadBatchLauncher = hipError_t (*)(const InvHeadBatch &, hipStream_t);
 
 template <int WV, int SCH, typename TIN, typename TLL, typename T>
 hipError_t launch_fwd_head_batch(const FwdHeadBatch &b, hipStream_t s) {
-    if constexpr (kFwdByWindows<WV>) {
+    if constexpr (kFwdByWindows<WV, T>) {
         if (b.h[0].seg == 0) {
             if (b.tile_start[b.n] <= 0) return hipSuccess;
-            hipLaunchKernelGGL((fwd_head_tile_batch_kernel<WV, SCH, kHeadTileRows, kHeadTileWaves, TIN, TLL, T>),
-                               dim3(b.tile_start[b.n]), dim3(64 * kHeadTileWaves), 0, s, b);
+            bool any_odd = false;
+            for (int i = 0; i < b.n; ++i) any_odd |= odd_rows(b.h[i]);
+            const auto k = pick_fwd_window<WV, T>(any_odd, [](auto odd) {
+                return &fwd_head_tile_batch_kernel<WV, SCH, kHeadTileRows, kHeadTileWaves, TIN, TLL,
+                                                   T, odd.value>;
+            });
+            hipLaunchKernelGGL(k, dim3(b.tile_start[b.n]), dim3(64 * kHeadTileWaves), 0, s, b);
             return hipGetLastError();
         }
     }
@@ -489,8 +521,13 @@ template <int WV, int SCH, typename TLL, typename T, typename TOUT>
 hipError_t launch_inv_head_batch(const InvHeadBatch &b, hipStream_t s) {
     if (b.h[0].seg == 0) {
         if (b.tile_start[b.n] <= 0) return hipSuccess;
-        hipLaunchKernelGGL((inv_head_tile_batch_kernel<WV, SCH, kHeadTileRows, kHeadTileWaves, TLL, T, TOUT>),
-                           dim3(b.tile_start[b.n]), dim3(64 * kHeadTileWaves), 0, s, b);
+        bool any_odd = false;
+        for (int i = 0; i < b.n; ++i) any_odd |= odd_rows(b.h[i]);
+        const auto k = pick_kernel<T>(any_odd, [](auto odd) {
+            return &inv_head_tile_batch_kernel<WV, SCH, kHeadTileRows, kHeadTileWaves, TLL, T, TOUT,
+                                               odd.value>;
+        });
+        hipLaunchKernelGGL(k, dim3(b.tile_start[b.n]), dim3(64 * kHeadTileWaves), 0, s, b);
         return hipGetLastError();
     }
     const int grid = head_blocks(b.tile_start[b.n]);

@@ -16,16 +16,18 @@ PARAMS = {0: 216, 1: 200}
 OWN, HALO = 48, 6
 
 
-def _head(sizes, dtype, wavelet, inverse):
-    """(segment, row pairs that a launch with it walks, and with 18) of a plan."""
+def _head(sizes, dtype, wavelet, inverse, pad=0):
+    """(segment, 0 for windows, row pairs that a launch with it walks, and with 18)
+    of a plan of images whose rows are `pad` elements longer."""
     lib = _lib.load()
     es = 4 if dtype == _lib.F32 else 2
     arr = (_lib.Image * len(sizes))()
     base = FAKE
     for i, (w, h) in enumerate(sizes):
         ws = lib.dwt2_workspace_bytes(w, h, 2, dtype)
-        arr[i] = _lib.Image(base, w, base + w * h * es, w, base + 2 * w * h * es, ws, w, h)
-        base += 2 * w * h * es + ws + 4096
+        p, n = w + pad, (w + pad) * h * es
+        arr[i] = _lib.Image(base, p, base + n, p, base + 2 * n + 2 * n % 4, ws, w, h)
+        base += 2 * n + ws + 4096 - n % 4
     n = ctypes.c_size_t()
     args = (arr, len(sizes), dtype, wavelet, 2, inverse, 0, None, _lib.PLAN_HEAD)
     assert lib.dwt2_batch_plan_bytes(*args, ctypes.byref(n)) == 0
@@ -57,3 +59,13 @@ def test_small_images_alone(dtype, inverse):
     for count in (1100, 4200, 8000):
         seg, walked, short = _head([(32, 32)] * count, dtype, 0, inverse)
         assert seg == 8 or seg == 0, seg     # no taller than the images
+
+
+@pytest.mark.parametrize("inverse", [0, 1])
+@pytest.mark.parametrize("wavelet", [0, 1])
+@pytest.mark.parametrize("dtype", [_lib.F16, _lib.BF16])
+def test_rows_at_odd_halves_of_a_word(dtype, wavelet, inverse):
+    """A launch of few windows runs by windows, whatever its rows start at."""
+    for sizes in ([(256, 256)], [(608, 128)], [(1024, 960), (64, 64)], [(2048, 2048)]):
+        assert _head(sizes, dtype, wavelet, inverse, pad=7)[0] == 0, sizes
+    assert _head([(16384, 16384)], dtype, wavelet, inverse, pad=7)[0] > 0
