@@ -380,22 +380,27 @@ int64_t head_windows(const HeadShape &im, bool inverse) {
 // window's time; one of many pays their halo and their phases in full, and
 // strips are faster. Measured, us by windows and by strips (bands in the caches
 // where they fit; from memory), the counts on 256 CUs:
-//   9/7 forward FP32: 75 windows 8.6, 9.2 (8.8, 9.3); 504: 13.8, 16.0 (17.9, 19.7);
-//     602: 17.7, 16.3 (23.7, 21.4); 261, in between: 12.2, 11.9 (14.5, 12.8)
-//   9/7 forward 16-bit: 240: 9.7, 12.2 (11.4, 12.3); 774: 18.8, 19.7 (21.5, 21.0);
-//     1026: 22.1, 23.1 (25.6, 24.9);
-//     1368: 26.4, 25.2 (32.5, 28.3)
-//   9/7 inverse FP32: 60: 8.6, 9.6 (8.9, 9.6); 490: 14.7, 17.3 (20.7, 21.7);
-//     630: 20.7, 20.3 (29.3, 27.3)
-//   9/7 inverse 16-bit: 216: 9.6, 12.8 (11.3, 13.1); 630: 18.9, 20.6 (23.2, 21.5);
-//     846: 23.1, 24.0 (29.8, 24.9); with streamed pixels, 630: 16.6, 19.7 (19.0, 20.1),
-//     954: 20.5, 24.8 (24.4, 25.9), 1512: 29.4, 31.9 (36.5, 35.4), 1890: 35.7, 34.5
-//     (47.1, 38.1)
-// The 5/3 strips carry half the stages and less halo, and are faster at every
-// size (forward: see kFwdByWindows; inverse FP32 72: 7.5, 6.2 (8.4, 6.5), 490: 13.8,
-// 13.6 (20.7, 19.7)) but one: 16-bit inverse, 72: 7.4, 6.3 (7.7, 6.3); 117: 7.6,
-// 8.0 (7.9, 8.0); 216: 8.3, 10.1 (10.1, 10.6); 342: 10.2, 11.0; 360: 11.9, 11.0
-// (14.8, 12.2).
+//   9/7 forward FP32: 75 windows 9.0, 9.7 (9.0, 9.6); 261: 11.6, 12.7 (14.4, 13.5);
+//     506: 15.3, 17.5 (20.3, 22.5); 552: 18.8, 18.2 (26.0, 22.2)
+//   9/7 forward 16-bit: 261: 11.3, 12.6 (12.6, 13.1); 648: 16.7, 19.2 (19.1, 20.1);
+//     1026: 22.0, 23.2 (25.5, 25.6); 1161: 23.3, 23.2 (28.5, 26.9); 1656: 29.3, 28.9
+//     (35.7, 33.8)
+//   9/7 inverse FP32: 60: 9.0, 10.4 (9.3, 10.3); 360: 15.2, 18.7 (20.4, 20.9); 506:
+//     18.2, 19.7 (21.2, 22.9); 552: 22.7, 19.9 (26.0, 24.3)
+//   9/7 inverse 16-bit: 216: 9.6, 13.3 (10.8, 13.6); 600: 17.8, 20.2 (20.8, 21.5); 930:
+//     21.6, 26.8 (27.0, 28.7); 1056: 25.8, 26.6 (31.2, 29.0); with streamed pixels, 930:
+//     20.3, 25.6 (25.0, 27.0); 1056: 24.0, 25.6 (28.7, 27.1)
+// The 5/3 strips carry half the stages and less halo. Forward they are faster at
+// every size (see kFwdByWindows); inverse, windows are where most of a round of
+// them is resident, one to a CU or two (FP32, whose rounds take longer: only
+// then):
+//   5/3 inverse 16-bit: 64: 7.5, 6.6 (7.6, 6.5); 90: 7.6, 8.2 (7.9, 8.1); 240: 8.5, 10.7
+//     (10.6, 11.3); 342: 10.7, 11.4 (13.0, 13.0); 506: 11.3, 13.7 (14.2, 15.7); 552: 14.9,
+//     13.8 (18.3, 15.8)
+//   5/3 inverse FP32: 64: 8.0, 6.9 (8.5, 7.0); 156: 9.2, 9.5 (12.2, 11.2); 195: 9.9, 11.2
+//     (13.1, 12.9); 240: 10.5, 11.6 (13.6, 13.7); 272: 13.0, 11.8 (17.3, 15.5); 380: 14.1,
+//     14.5 (20.0, 19.7); 420: 14.6, 14.5 (18.4, 19.1); 506: 16.7, 16.6 (20.0, 21.4); 552:
+//     20.3, 17.7 (25.0, 24.0)
 // FP32 9/7 forward strips whose band rows are off the 64-byte sectors write parts
 // of lines at every piece end, and lose to windows again where those are many:
 // pitch of 28 bytes more, 1026 windows: 35.6, 34.4; 1848: 58.3, 61.7; 4104: 112.9,
@@ -412,14 +417,16 @@ int64_t head_windows(const HeadShape &im, bool inverse) {
 //   5/3 inverse 490: 13.4, 19.3 (16.3, 21.6); 846: 21.6, 22.8 (26.4, 27.6); 1260: 28.5,
 //     28.2 (36.5, 36.1)
 bool head_by_windows(const HeadShape *im, int n, int wavelet, bool wide, bool inverse, bool odd,
-                     bool streamed, bool off_sectors) {
+                     bool off_sectors) {
     const int64_t cus = device_cus();
     int64_t w = 0;
     for (int i = 0; i < n; ++i) w += head_windows(im[i], inverse);
     if (odd) return 2 * w <= cus * (wavelet == DWT2_CDF97 ? 16 : inverse ? 8 : 5);
     if (wavelet == DWT2_CDF97 && wide && !inverse && off_sectors && w > 6 * cus) return true;
-    if (wavelet == DWT2_CDF97) return w <= cus * (wide ? 2 : !inverse ? 5 : streamed ? 6 : 3);
-    return inverse && !wide && 8 * w > 3 * cus && 8 * w <= 11 * cus;
+    if (wavelet == DWT2_CDF97) return 2 * w <= cus * (wide ? 4 : inverse ? 8 : 9);
+    if (!inverse) return false;
+    if (!wide) return 8 * w > 3 * cus && w <= 2 * cus;
+    return (4 * w > 3 * cus && w <= cus) || (2 * w > 3 * cus && w <= 2 * cus);
 }
 // Whether level j band rows start off the 64-byte sectors (forward).
 bool head_off_sectors(const FwdHead &h) {
@@ -433,7 +440,7 @@ bool head_off_sectors(const InvHead &) { return false; }
 // one odd image among them as without).
 int head_layout(const HeadShape *im, int n, int wavelet, bool wide, bool inverse, bool odd,
                 bool streamed = false, bool off_sectors = false) {
-    return head_by_windows(im, n, wavelet, wide, inverse, odd, streamed, off_sectors)
+    return head_by_windows(im, n, wavelet, wide, inverse, odd, off_sectors)
                ? 0 : head_segment(im, n, wavelet, wide, inverse, streamed);
 }
 

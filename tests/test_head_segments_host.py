@@ -6,6 +6,7 @@ import ctypes
 import struct
 
 import pytest
+import torch
 
 from paper_1705_08266_amd import _lib
 
@@ -69,3 +70,20 @@ def test_rows_at_odd_halves_of_a_word(dtype, wavelet, inverse):
     for sizes in ([(256, 256)], [(608, 128)], [(1024, 960), (64, 64)], [(2048, 2048)]):
         assert _head(sizes, dtype, wavelet, inverse, pad=7)[0] == 0, sizes
     assert _head([(16384, 16384)], dtype, wavelet, inverse, pad=7)[0] > 0
+
+
+@pytest.mark.parametrize("wavelet,dtype,inverse,windows,strips", [
+    (0, _lib.F32, 0, [1, 2], [2.25]), (0, _lib.F32, 1, [1, 2], [2.25]),
+    (0, _lib.F16, 0, [1, 4.5], [4.75]), (0, _lib.F16, 1, [3.25, 4], [4.25]),
+    (1, _lib.F16, 1, [0.5, 1.5, 2], [0.25, 2.25]),
+    (1, _lib.F32, 1, [0.875, 1, 1.75, 2], [0.5, 1.25, 2.25]),
+    (1, _lib.F16, 0, [], [0.5, 2]), (1, _lib.F32, 0, [], [0.5, 2])])
+def test_windows_or_strips(wavelet, dtype, inverse, windows, strips):
+    """Windows per compute unit at which a launch runs by either, one window across."""
+    cus = 256                      # where no device says otherwise
+    if torch.cuda.is_available():
+        cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rows = 88 if inverse else 72
+    for per_cu in windows + strips:
+        seg = _head([(232, int(per_cu * cus) * rows)], dtype, wavelet, inverse)[0]
+        assert (seg == 0) == (per_cu in windows), per_cu
