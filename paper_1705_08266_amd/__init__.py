@@ -113,6 +113,21 @@ def workspace_bytes(width: int, height: int, levels: int, dtype=_lib.F32) -> int
     return int(load().dwt2_workspace_bytes(width, height, levels, int(dtype)))
 
 
+def _workspace_size(width: int, height: int, levels) -> int:
+    """Floats of workspace, looked up by value; levels that are no plain int
+    (anything ctypes takes for one, a tensor or an array among them) are asked
+    for each time."""
+    if type(levels) is not int:
+        return workspace_bytes(width, height, levels) // 4
+    key = (width, height, levels)
+    n = _workspace_floats.get(key)
+    if n is None:
+        if len(_workspace_floats) >= _CACHE_MAX:
+            _workspace_floats.clear()
+        n = _workspace_floats[key] = workspace_bytes(*key) // 4
+    return n
+
+
 def make_workspace(width: int, height: int, levels: int, device=None):
     torch = _torch()
     n = workspace_bytes(width, height, levels)
@@ -127,12 +142,7 @@ def _transform(plain, hooked, src, name, wavelet, levels, scheme, out, workspace
         out = torch.empty_like(src)
     _check_2d(out, "out")
     if workspace is None:
-        key = (src.shape[1], src.shape[0], levels)
-        n = _workspace_floats.get(key)
-        if n is None:
-            if len(_workspace_floats) >= _CACHE_MAX:
-                _workspace_floats.clear()
-            n = _workspace_floats[key] = workspace_bytes(*key) // 4
+        n = _workspace_size(src.shape[1], src.shape[0], levels)
         if n:
             workspace = torch.empty(n, dtype=torch.float32, device=src.device)
     if workspace is not None:
