@@ -39,16 +39,15 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 METRIC = ("Gpixel/s fwd+inv CDF 9/7 DWT at 4096², 5 levels (% HBM peak); "
           "serving p50/p99")
-# Traffic counters are valid for the kernel code they were taken with (these
-# sources) and the tile geometry named in their key.
-KERNEL_SOURCES = ("dwt2_device.hpp", "dwt2_kernels.hpp", "dwt2_head.hpp", "dwt2_tail.hpp")
-
-
-def kernel_source_sha() -> str:
+# Traffic counters are valid for the kernel code they were taken with (every
+# header), the layout that its launches get (the C entry points) and the image
+# named in their key.
+def kernel_source_sha(csrc=os.path.join(ROOT, "paper_1705_08266_amd", "csrc")) -> str:
     h = hashlib.sha256()
-    for n in KERNEL_SOURCES:
-        with open(os.path.join(ROOT, "paper_1705_08266_amd", "csrc", n), "rb") as f:
-            h.update(f.read())
+    for n in sorted(os.listdir(csrc)):
+        if n.endswith(".hpp") or n == "dwt2_api.hip":
+            with open(os.path.join(csrc, n), "rb") as f:
+                h.update(n.encode() + b"\0" + f.read())
     return h.hexdigest()[:16]
 
 
