@@ -419,18 +419,18 @@ __global__ __launch_bounds__(64 * kHeadWaves) void inv_head_kernel(InvHead hd, i
 template <int WV, int SCH, typename TIN, typename TLL, typename TB>
 __global__ __launch_bounds__(64 * kHeadWaves) void fwd_head_table_kernel(TableLaunch<FwdHead> tl) {
     for (int t = head_slot(); t < tl.total; t += gridDim.x * kHeadWaves) {
-        const int i = __builtin_amdgcn_readfirstlane(tl.img[t]);
-        const FwdHead hd = tl.params[i];
-        fwd_head_task<WV, SCH, kHeadOwn, TIN, TLL, TB, false>(hd, t - tl.start[i]);
+        const int i = load_uniform(tl.img + t);
+        const FwdHead hd = load_uniform(tl.params + i);
+        fwd_head_task<WV, SCH, kHeadOwn, TIN, TLL, TB, false>(hd, t - load_uniform(tl.start + i));
     }
 }
 
 template <int WV, int SCH, typename TLL, typename TB, typename TOUT>
 __global__ __launch_bounds__(64 * kHeadWaves) void inv_head_table_kernel(TableLaunch<InvHead> tl) {
     for (int t = head_slot(); t < tl.total; t += gridDim.x * kHeadWaves) {
-        const int i = __builtin_amdgcn_readfirstlane(tl.img[t]);
-        const InvHead hd = tl.params[i];
-        inv_head_task<WV, SCH, kHeadOwn, TLL, TB, TOUT, false>(hd, t - tl.start[i]);
+        const int i = load_uniform(tl.img + t);
+        const InvHead hd = load_uniform(tl.params + i);
+        inv_head_task<WV, SCH, kHeadOwn, TLL, TB, TOUT, false>(hd, t - load_uniform(tl.start + i));
     }
 }
 

@@ -158,9 +158,9 @@ __device__ __forceinline__ void fwd_head_tile(const FwdHead &hd, const int t,
             const float vb[2] = {q.b[r][0] * sHL, q.b[r][1] * sHL};
             const float vc[2] = {q.c[r][0] * sHL, q.c[r][1] * sHL};
             const float vd[2] = {q.d[r][0] * sHH, q.d[r][1] * sHH};
-            store_cols<TB, 2>(hl + rowo, p1.nqx, qx, own_x, !ODD, vb);
-            store_cols<TB, 2>(lh + rowo, p1.nqx, qx, own_x, !ODD, vc);
-            store_cols<TB, 2>(hh + rowo, p1.nqx, qx, own_x, !ODD, vd);
+            store_cols<TB, 2, kStoreCached, false>(hl + rowo, p1.nqx, qx, own_x, !ODD, vb);
+            store_cols<TB, 2, kStoreCached, false>(lh + rowo, p1.nqx, qx, own_x, !ODD, vc);
+            store_cols<TB, 2, kStoreCached, false>(hh + rowo, p1.nqx, qx, own_x, !ODD, vd);
         }
     }
 
@@ -331,11 +331,11 @@ __device__ __forceinline__ void inv_head_tile(const InvHead &hd, const int t,
         TOUT *r0p = out + ro;
         TOUT *r1p = r0p + p1.out_pitch;
         if (p1.stream_out) {
-            store_cols<TOUT, 4, kStoreStream>(r0p, p1.w, px0, on, !ODD, e);
-            store_cols<TOUT, 4, kStoreStream>(r1p, p1.w, px0, on, !ODD, o);
+            store_cols<TOUT, 4, kStoreStream, false>(r0p, p1.w, px0, on, !ODD, e);
+            store_cols<TOUT, 4, kStoreStream, false>(r1p, p1.w, px0, on, !ODD, o);
         } else {
-            store_cols<TOUT, 4>(r0p, p1.w, px0, on, !ODD, e);
-            store_cols<TOUT, 4>(r1p, p1.w, px0, on, !ODD, o);
+            store_cols<TOUT, 4, kStoreCached, false>(r0p, p1.w, px0, on, !ODD, e);
+            store_cols<TOUT, 4, kStoreCached, false>(r1p, p1.w, px0, on, !ODD, o);
         }
     }
 }
@@ -364,9 +364,9 @@ __global__ __launch_bounds__(64 * WAVES, kTableHeadWavesPerSimd<WAVES>) void fwd
     TableLaunch<FwdHead> tl) {
     __shared__ FwdTileLds<ROWS, WAVES> lds;
     for (int t = block_tile(); t < tl.total; t += gridDim.x) {
-        const int i = __builtin_amdgcn_readfirstlane(tl.img[t]);
-        const FwdHead hd = tl.params[i];
-        fwd_head_tile<WV, SCH, ROWS, WAVES, TIN, TLL, TB, ODD>(hd, t - tl.start[i], lds);
+        const int i = load_uniform(tl.img + t);
+        const FwdHead hd = load_uniform(tl.params + i);
+        fwd_head_tile<WV, SCH, ROWS, WAVES, TIN, TLL, TB, ODD>(hd, t - load_uniform(tl.start + i), lds);
         __syncthreads();
     }
 }
@@ -376,9 +376,9 @@ __global__ __launch_bounds__(64 * WAVES, kTableHeadWavesPerSimd<WAVES>) void inv
     TableLaunch<InvHead> tl) {
     __shared__ InvTileLds<ROWS, WAVES> lds;
     for (int t = block_tile(); t < tl.total; t += gridDim.x) {
-        const int i = __builtin_amdgcn_readfirstlane(tl.img[t]);
-        const InvHead hd = tl.params[i];
-        inv_head_tile<WV, SCH, ROWS, WAVES, TLL, TB, TOUT, ODD>(hd, t - tl.start[i], lds);
+        const int i = load_uniform(tl.img + t);
+        const InvHead hd = load_uniform(tl.params + i);
+        inv_head_tile<WV, SCH, ROWS, WAVES, TLL, TB, TOUT, ODD>(hd, t - load_uniform(tl.start + i), lds);
         __syncthreads();
     }
 }

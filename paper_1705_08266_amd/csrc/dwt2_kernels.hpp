@@ -215,25 +215,30 @@ __device__ __forceinline__ void fwd_store(const Quads<ROWS, QPL> &q, const FwdPa
     TB *hl = static_cast<TB *>(prm.hl);
     TB *lh = static_cast<TB *>(prm.lh);
     TB *hh = static_cast<TB *>(prm.hh);
-    // element offsets of row qy0 + r, stepped
-    int64_t rowb = (int64_t)qy0 * prm.band_pitch, rowl = (int64_t)qy0 * prm.ll_pitch;
+    const auto rows = [&](auto ragged) {
+        constexpr bool RAGGED = decltype(ragged)::value;
+        // element offsets of row qy0 + r, stepped
+        int64_t rowb = (int64_t)qy0 * prm.band_pitch, rowl = (int64_t)qy0 * prm.ll_pitch;
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r, rowb += prm.band_pitch, rowl += prm.ll_pitch) {
-        const int wr = wave * ROWS + r;
-        const int gy = qy0 + r;
-        if (wr < G::HY || wr >= WAVES * ROWS - G::HY || gy >= prm.nqy) continue;
-        float va[QPL], vb[QPL], vc[QPL], vd[QPL];
+        for (int r = 0; r < ROWS; ++r, rowb += prm.band_pitch, rowl += prm.ll_pitch) {
+            const int wr = wave * ROWS + r;
+            const int gy = qy0 + r;
+            if (wr < G::HY || wr >= WAVES * ROWS - G::HY || gy >= prm.nqy) continue;
+            float va[QPL], vb[QPL], vc[QPL], vd[QPL];
 #pragma unroll
-        for (int i = 0; i < QPL; ++i) {
-            va[i] = q.a[r][i] * sLL; vb[i] = q.b[r][i] * sHL;
-            vc[i] = q.c[r][i] * sHL; vd[i] = q.d[r][i] * sHH;
+            for (int i = 0; i < QPL; ++i) {
+                va[i] = q.a[r][i] * sLL; vb[i] = q.b[r][i] * sHL;
+                vc[i] = q.c[r][i] * sHL; vd[i] = q.d[r][i] * sHH;
+            }
+            const bool on = qx0 < prm.nqx;
+            store_cols<TLL, QPL, kStoreCached, RAGGED>(ll + rowl, prm.nqx, qx0, on, !ODD, va);
+            store_cols<TB, QPL, kStoreCached, RAGGED>(hl + rowb, prm.nqx, qx0, on, !ODD, vb);
+            store_cols<TB, QPL, kStoreCached, RAGGED>(lh + rowb, prm.nqx, qx0, on, !ODD, vc);
+            store_cols<TB, QPL, kStoreCached, RAGGED>(hh + rowb, prm.nqx, qx0, on, !ODD, vd);
         }
-        const bool on = qx0 < prm.nqx;
-        store_cols<TLL, QPL>(ll + rowl, prm.nqx, qx0, on, !ODD, va);
-        store_cols<TB, QPL>(hl + rowb, prm.nqx, qx0, on, !ODD, vb);
-        store_cols<TB, QPL>(lh + rowb, prm.nqx, qx0, on, !ODD, vc);
-        store_cols<TB, QPL>(hh + rowb, prm.nqx, qx0, on, !ODD, vd);
-    }
+    };
+    if (sizeof(TB) == 4 || (prm.nqx & (QPL - 1)) == 0) rows(std::false_type{});
+    else rows(std::true_type{});
 }
 
 // One tile of a forward level: load, lift, store. All waves of the
@@ -352,27 +357,35 @@ __device__ __forceinline__ void inv_store(const Quads<ROWS, QPL> &q, const InvPa
     TOUT *out = static_cast<TOUT *>(prm.out);
     const int px0 = 2 * qx0;
     const bool on = px0 < prm.w;
-    int64_t ro = (int64_t)(2 * qy0) * prm.out_pitch;   // pixel row 2 (qy0 + r), stepped
+    const auto rows = [&](auto policy, auto ragged) {
+        constexpr int POLICY = decltype(policy)::value;
+        constexpr bool RAGGED = decltype(ragged)::value;
+        int64_t ro = (int64_t)(2 * qy0) * prm.out_pitch;   // pixel row 2 (qy0 + r), stepped
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r, ro += 2 * prm.out_pitch) {
-        const int wr = wave * ROWS + r;
-        const int gy = qy0 + r;
-        if (wr < G::HY || wr >= WAVES * ROWS - G::HY || gy >= prm.nqy) continue;
-        float e[2 * QPL], o[2 * QPL];
+        for (int r = 0; r < ROWS; ++r, ro += 2 * prm.out_pitch) {
+            const int wr = wave * ROWS + r;
+            const int gy = qy0 + r;
+            if (wr < G::HY || wr >= WAVES * ROWS - G::HY || gy >= prm.nqy) continue;
+            float e[2 * QPL], o[2 * QPL];
 #pragma unroll
-        for (int i = 0; i < QPL; ++i) {
-            e[2 * i] = q.a[r][i] * up; e[2 * i + 1] = q.b[r][i] * up;
-            o[2 * i] = q.c[r][i] * up; o[2 * i + 1] = q.d[r][i] * up;
+            for (int i = 0; i < QPL; ++i) {
+                e[2 * i] = q.a[r][i] * up; e[2 * i + 1] = q.b[r][i] * up;
+                o[2 * i] = q.c[r][i] * up; o[2 * i + 1] = q.d[r][i] * up;
+            }
+            TOUT *r0 = out + ro;
+            TOUT *r1 = r0 + prm.out_pitch;
+            store_cols<TOUT, 2 * QPL, POLICY, RAGGED>(r0, prm.w, px0, on, !ODD, e);
+            store_cols<TOUT, 2 * QPL, POLICY, RAGGED>(r1, prm.w, px0, on, !ODD, o);
         }
-        TOUT *r0 = out + ro;
-        TOUT *r1 = r0 + prm.out_pitch;
-        if (prm.stream_out) {
-            store_cols<TOUT, 2 * QPL, kStoreStream>(r0, prm.w, px0, on, !ODD, e);
-            store_cols<TOUT, 2 * QPL, kStoreStream>(r1, prm.w, px0, on, !ODD, o);
-        } else {
-            store_cols<TOUT, 2 * QPL>(r0, prm.w, px0, on, !ODD, e);
-            store_cols<TOUT, 2 * QPL>(r1, prm.w, px0, on, !ODD, o);
-        }
+    };
+    const std::integral_constant<int, kStoreStream> stream;
+    const std::integral_constant<int, kStoreCached> cached;
+    if (sizeof(TOUT) == 4 || (prm.w & (2 * QPL - 1)) == 0) {
+        if (prm.stream_out) rows(stream, std::false_type{});
+        else rows(cached, std::false_type{});
+    } else {
+        if (prm.stream_out) rows(stream, std::true_type{});
+        else rows(cached, std::true_type{});
     }
 }
 
@@ -488,6 +501,26 @@ struct TableLaunch {
     int32_t total;          // tiles of the launch
 };
 
+// *p for a wavefront-uniform p into memory that the launch does not write, by
+// scalar loads. The compiler loads it per lane (it cannot rule out that a store
+// of the same loop changes it), and then takes addresses and resources made from
+// it for different in every lane: loops around buffer accesses, each with a wait
+// (32 images of sides up to 4096, one level from memory: FP16 inverse 28.8 us so,
+// 19.7 with scalar loads in 5/3, 31.8 and 22.3 in 9/7; forward 26.2 and 22.0, 29.5
+// and 25.1).
+template <typename P>
+__device__ __forceinline__ P load_uniform(const P *p) {
+    typedef const __attribute__((address_space(4))) uint32_t Constant;
+    static_assert(sizeof(P) % 4 == 0 && alignof(P) >= 4, "whole words");
+    Constant *s = (Constant *)(uintptr_t)p;
+    uint32_t w[sizeof(P) / 4];
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(P) / 4; ++k) w[k] = s[k];
+    P r;
+    __builtin_memcpy(&r, w, sizeof r);
+    return r;
+}
+
 // Every workgroup walks the tiles t = its id, id + gridDim.x, ... below
 // `total`: one tile each when the grid has one workgroup per tile, several
 // when the grid is capped at the resident workgroups (persistent).
@@ -498,9 +531,10 @@ __global__ __launch_bounds__(64 * WAVES) void fwd_table_kernel(TableLaunch<FwdPa
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int t = block_tile(); t < tl.total; t += gridDim.x) {
-        const int i = __builtin_amdgcn_readfirstlane(tl.img[t]);
-        const FwdParams prm = tl.params[i];
-        fwd_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB, ODD>(prm, t - tl.start[i], box, lane, wave);
+        const int i = load_uniform(tl.img + t);
+        const FwdParams prm = load_uniform(tl.params + i);
+        fwd_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB, ODD>(prm, t - load_uniform(tl.start + i), box,
+                                                               lane, wave);
     }
 }
 
@@ -511,9 +545,10 @@ __global__ __launch_bounds__(64 * WAVES) void inv_table_kernel(TableLaunch<InvPa
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int t = block_tile(); t < tl.total; t += gridDim.x) {
-        const int i = __builtin_amdgcn_readfirstlane(tl.img[t]);
-        const InvParams prm = tl.params[i];
-        inv_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT, ODD>(prm, t - tl.start[i], box, lane, wave);
+        const int i = load_uniform(tl.img + t);
+        const InvParams prm = load_uniform(tl.params + i);
+        inv_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT, ODD>(prm, t - load_uniform(tl.start + i), box,
+                                                               lane, wave);
     }
 }
 

@@ -276,8 +276,9 @@ __global__ __launch_bounds__(64 * kTailWaves) void inv_tail_kernel(InvTail t) {
                     const float e[2] = {q.a[r][0] * up, q.b[r][0] * up};
                     const float o[2] = {q.c[r][0] * up, q.d[r][0] * up};
                     const TOUT *r0 = static_cast<const TOUT *>(prm.out) + ro;
-                    store_cols<TOUT, 2>(r0, prm.w, 2 * qx, own_x, prm.vec_out, e);
-                    store_cols<TOUT, 2>(r0 + prm.out_pitch, prm.w, 2 * qx, own_x, prm.vec_out, o);
+                    store_cols<TOUT, 2, kStoreCached, false>(r0, prm.w, 2 * qx, own_x, prm.vec_out, e);
+                    store_cols<TOUT, 2, kStoreCached, false>(r0 + prm.out_pitch, prm.w, 2 * qx, own_x,
+                                                             prm.vec_out, o);
                 }
             } else if (comp_x && gy >= g.cy0 && gy < g.cy1) {
                 float *p0 = dst + (2 * (gy - g.cy0)) * cw + 2 * (qx - g.cx0);
