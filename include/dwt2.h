@@ -186,6 +186,17 @@ int dwt2_fused_levels(int32_t width, int32_t height, int32_t levels);
  * rejects. */
 int dwt2_head_levels(int32_t width, int32_t height, int32_t levels);
 
+/* How a fused head of levels 1 and 2 is laid out on the current device (256
+ * compute units where there is none) in dwt2_forward (inverse = 0) or
+ * dwt2_inverse (1) of these buffers, which are not accessed. It runs by strips
+ * of 48 level 2 columns cut into segments of *rows rows of level 2, or where
+ * *rows is 0 by windows of 58 x 18 (inverse: 58 x 22) of them; *tasks is how
+ * many there are, and *streamed whether the bands of level 1 and 2 (forward) or
+ * the pixels are stored past the caches. Each result may be NULL. */
+int dwt2_head_layout(const void *src, const dwt2_desc *src_d, const void *dst,
+                     const dwt2_desc *dst_d, dwt2_wavelet wavelet, int32_t levels, int32_t inverse,
+                     int32_t *rows, int32_t *tasks, int32_t *streamed);
+
 /* dwt2_forward (dwt2_inverse) with two tuning and timing hooks; results are
  * identical to the plain calls.
  *   tiles : NULL to let the library choose, else `levels` tile ids

@@ -252,5 +252,17 @@ def head_levels(width: int, height: int, levels: int) -> int:
     return n
 
 
+def head_layout(src, dst, wavelet="cdf97", levels: int = 2, inverse=False):
+    """(rows, tasks, streamed) of a fused head of levels 1 and 2 of
+    forward(src, out=dst) or inverse(src, out=dst): rows of level 2 to a segment
+    of its strips (0: it runs by windows), strips times segments (or windows),
+    and whether its results are stored past the caches."""
+    v = [ctypes.c_int32() for _ in range(3)]
+    _lib.check(load().dwt2_head_layout(src.data_ptr(), _desc(src), dst.data_ptr(), _desc(dst),
+                                       _wavelet(wavelet), levels, int(bool(inverse)),
+                                       *[ctypes.byref(a) for a in v]), "dwt2_head_layout")
+    return v[0].value, v[1].value, bool(v[2].value)
+
+
 def default_tile(width, height, wavelet="cdf97", scheme="nonseparable", dtype=_lib.F32):
     return int(load().dwt2_default_tile(width, height, _wavelet(wavelet), _scheme(scheme), dtype))

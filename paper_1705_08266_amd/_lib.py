@@ -97,6 +97,8 @@ SIGNATURES = {
     "dwt2_inverse_head_batch": (ctypes.c_int, [_LevelJobP, _i32, _i32, _i32, _vp]),
     "dwt2_fused_levels": (ctypes.c_int, [_i32, _i32, _i32]),
     "dwt2_head_levels": (ctypes.c_int, [_i32, _i32, _i32]),
+    "dwt2_head_layout": (ctypes.c_int, [_vp, _DescP, _vp, _DescP, _i32, _i32, _i32,
+                                        _ip32, _ip32, _ip32]),
     "dwt2_status_string": (ctypes.c_char_p, [ctypes.c_int]),
     "dwt2_last_hip_error": (ctypes.c_int, []),
     "dwt2_version": (ctypes.c_int, []),

@@ -176,6 +176,11 @@ int pick_tile(int width, int height, int wavelet, int storage) {
 // cached for its reader, often an inverse.
 constexpr int64_t kCacheBytes = (int64_t)256 << 20;   // Infinity Cache
 constexpr int64_t kStreamOutMinBytes = (int64_t)32 << 20;
+// Whether the head of an image of so many bytes streams its bands (forward, by
+// strips: windows do not) or its pixels (inverse).
+bool head_streams(bool inverse, int64_t bytes) {
+    return inverse ? bytes >= kStreamOutMinBytes : bytes > kCacheBytes;
+}
 
 const FwdTable &fwd_table(int dt) {
     return dt == DWT2_F32 ? kFwdF32 : dt == DWT2_F16 ? kFwdF16 : kFwdBF16;
@@ -1067,6 +1072,45 @@ int dwt2_head_levels(int32_t width, int32_t height, int32_t levels) {
     return use_head(levels, nullptr, tail_start(width, height, levels, nullptr), 0) ? 2 : 0;
 }
 
+int dwt2_head_layout(const void *src, const dwt2_desc *src_d, const void *dst,
+                     const dwt2_desc *dst_d, dwt2_wavelet wavelet, int32_t levels, int32_t inverse,
+                     int32_t *rows, int32_t *tasks, int32_t *streamed) {
+    const int st = check_multi(src, src_d, dst, dst_d, wavelet, levels,
+                               DWT2_EXT_WHOLE_SAMPLE_SYMMETRIC, DWT2_NONSEPARABLE, nullptr,
+                               nullptr, 0);
+    if (st != DWT2_OK && st != DWT2_ERR_WORKSPACE) return st;
+    if (levels < 2 || (inverse != 0 && inverse != 1)) return DWT2_ERR_INVALID_ARG;
+    const int32_t W = src_d->width, H = src_d->height, T = src_d->dtype;
+    const size_t es = elem_size(T);
+    const dwt2_desc *pd = inverse ? src_d : dst_d;   // the pyramid
+    const char *cb = static_cast<const char *>(inverse ? src : dst);
+    const char *hl = cb + (size_t)(W / 2) * es;
+    const char *lh = cb + (size_t)((int64_t)(H / 2) * pd->pitch) * es;
+    const char *hh = lh + (size_t)(W / 2) * es;
+    const bool stream = head_streams(inverse, (int64_t)W * H * (int64_t)es);
+    int32_t n, seg;
+    if (inverse) {   // the band between the levels is not looked at
+        InvHead h;
+        h.l1 = inv_params(nullptr, W / 2, DWT2_F32, hl, lh, hh, pd->pitch, T,
+                          const_cast<void *>(dst), dst_d->pitch, T, W, H, wavelet, 0);
+        h.l2.nqx = W / 4; h.l2.nqy = H / 4;
+        n = head_grid_one(h, wavelet, T, true, stream);
+        seg = h.seg;
+    } else {
+        FwdHead h;
+        h.l1 = fwd_params(src, src_d->pitch, T, W, H, nullptr, W / 2, DWT2_F32,
+                          const_cast<char *>(hl), const_cast<char *>(lh), const_cast<char *>(hh),
+                          pd->pitch, T, wavelet, 0);
+        h.l2.nqx = W / 4; h.l2.nqy = H / 4;
+        n = head_grid_one(h, wavelet, T, false, stream);
+        seg = h.seg;
+    }
+    if (rows) *rows = seg;
+    if (tasks) *tasks = n;
+    if (streamed) *streamed = stream && (inverse || seg);
+    return DWT2_OK;
+}
+
 int dwt2_tile_config_count(void) { return kNumTiles; }
 
 int dwt2_tile_config_info(int32_t tile, dwt2_wavelet wavelet, int32_t *quads_per_lane, int32_t *rows,
@@ -1160,7 +1204,7 @@ int dwt2_forward_ex(const void *src, const dwt2_desc *src_d, void *coef, const d
             (j == 1 ? hd.l1 : hd.l2) = fwd_params(in, in_pitch, in_dt, w, h, ll, ll_pitch, ll_dt,
                                                   hl, lh, hh, cp, T, wavelet, 0);
             if (j == 1) continue;
-            const bool stream_bands = (int64_t)W * H * (int64_t)es > kCacheBytes;
+            const bool stream_bands = head_streams(false, (int64_t)W * H * (int64_t)es);
             const int tasks = head_grid_one(hd, wavelet, T, false, stream_bands);
             if ((st = record(level_events, 0, s))) return st;
             const hipError_t e =
@@ -1273,7 +1317,7 @@ int dwt2_inverse_ex(const void *coef, const dwt2_desc *coef_d, void *dst, const 
             (j == 2 ? hd.l2 : hd.l1) = inv_params(ll, ll_pitch, ll_dt, hl, lh, hh, cp, T, out,
                                                   out_pitch, out_dt, w, h, wavelet, 0);
             if (j == 2) continue;
-            const bool stream_pixels = image_bytes >= kStreamOutMinBytes;
+            const bool stream_pixels = head_streams(true, image_bytes);
             hd.l1.stream_out = stream_pixels;
             const int tasks = head_grid_one(hd, wavelet, T, true, stream_pixels);
             if ((st = record(level_events, 0, s))) return st;
