@@ -659,12 +659,10 @@ bool batch_images_conflict(const dwt2_image *images, int n, int dtype, int level
 // header, one PlanLaunch per launch, then per launch the tile -> image map,
 // each image's first tile and the images' level parameters. Offsets are from
 // the start of the plan; sections are 256-byte aligned.
-// A head launch's tile map counts windows (dwt2_head_tile.hpp). Where it runs
-// strips (dwt2_head.hpp) instead, a section after the parameters holds their
-// map: their number (in a 16-byte field; 0: the launch runs windows), each
-// image's first one, and the image of each.
+// The tiles of a head launch are its windows (dwt2_head_tile.hpp), or the strips
+// of its segments (dwt2_head.hpp) where its images' parameters name a segment.
 constexpr uint32_t kPlanMagic = 0x42545744u;   // "DWTB"
-constexpr int32_t kPlanVersion = 3;
+constexpr int32_t kPlanVersion = 4;
 
 struct PlanHeader {
     uint32_t magic;
@@ -697,13 +695,13 @@ bool any_odd_rows(const void *plan, const PlanLaunch &l) {
     return odd;
 }
 
-// The strip section of a head launch.
 size_t head_param_size(int inverse) { return inverse ? sizeof(InvHead) : sizeof(FwdHead); }
-size_t off_strips(const PlanLaunch &l, int inverse) {
-    return align256(l.off_params + head_param_size(inverse) * (size_t)l.images);
-}
-size_t strips_bytes(size_t images, size_t strips) {
-    return strips ? 16 + 4 * images + 4 * strips : 16;
+
+// Rows per segment of a head launch (0: windows; plan: its host copy).
+int head_plan_segment(const void *plan, const PlanLaunch &l, int inverse) {
+    const char *p = static_cast<const char *>(plan) + l.off_params;
+    return inverse ? reinterpret_cast<const InvHead *>(p)->seg
+                   : reinterpret_cast<const FwdHead *>(p)->seg;
 }
 
 const FwdHeadPlanTable &fwd_head_plan_table(int dt) {
@@ -746,13 +744,6 @@ int check_plan(const void *plan, size_t bytes, const PlanHeader **out) {
             l.off_start + 4 * (uint64_t)l.images > bytes ||
             l.off_params + psize * (uint64_t)l.images > bytes)
             return DWT2_ERR_INVALID_ARG;
-        if (head) {
-            const size_t off = off_strips(l, h->inverse);
-            if (off + 16 > bytes) return DWT2_ERR_INVALID_ARG;
-            int32_t n;
-            std::memcpy(&n, static_cast<const char *>(plan) + off, sizeof n);
-            if (n < 0 || off + strips_bytes(l.images, n) > bytes) return DWT2_ERR_INVALID_ARG;
-        }
     }
     *out = h;
     return DWT2_OK;
@@ -791,7 +782,6 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
         std::vector<InvParams> ip;
         std::vector<FwdHead> fh;
         std::vector<InvHead> ih;
-        std::vector<int32_t> strip_img, strip_start;   // head launches
     };
     std::vector<Group> groups;
     // one head launch over every image: levels 1 and 2, as dwt2_forward /
@@ -853,14 +843,9 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
             return DWT2_ERR_INVALID_ARG;
         for (int i = 0; i < n; ++i) {
             const int tasks = inverse ? head_grid(G.ih[i], seg) : head_grid(G.fh[i], seg);
-            if (seg) {
-                G.strip_start.push_back((int32_t)G.strip_img.size());
-                G.strip_img.insert(G.strip_img.end(), (size_t)tasks, (int32_t)i);
-            }
-            const int64_t tiles = head_windows(shapes[i], inverse);
             G.start.push_back((int32_t)G.img.size());
-            if ((int64_t)G.img.size() + tiles > (int64_t)INT32_MAX) return DWT2_ERR_INVALID_ARG;
-            G.img.insert(G.img.end(), (size_t)tiles, (int32_t)i);
+            if ((int64_t)G.img.size() + tasks > (int64_t)INT32_MAX) return DWT2_ERR_INVALID_ARG;
+            G.img.insert(G.img.end(), (size_t)tasks, (int32_t)i);
         }
         groups.push_back(std::move(G));
         return DWT2_OK;
@@ -944,8 +929,6 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
         G.l.off_params = off;
         off = align256(off + sizeof(InvParams) * G.ip.size() + sizeof(FwdParams) * G.fp.size() +
                        sizeof(InvHead) * G.ih.size() + sizeof(FwdHead) * G.fh.size());
-        if (!G.ih.empty() || !G.fh.empty())
-            off = align256(off + strips_bytes(G.strip_start.size(), G.strip_img.size()));
     }
     out.assign(off, 0);
     PlanHeader h{kPlanMagic, kPlanVersion, n, levels, inverse, dtype, wavelet,
@@ -962,14 +945,6 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
         if (!G.fh.empty()) std::memcpy(prm, G.fh.data(), sizeof(FwdHead) * G.fh.size());
         if (!G.ip.empty()) std::memcpy(prm, G.ip.data(), sizeof(InvParams) * G.ip.size());
         if (!G.fp.empty()) std::memcpy(prm, G.fp.data(), sizeof(FwdParams) * G.fp.size());
-        if (!G.strip_img.empty()) {
-            unsigned char *st = out.data() + off_strips(G.l, inverse);
-            const int32_t strips = (int32_t)G.strip_img.size();
-            std::memcpy(st, &strips, sizeof strips);
-            std::memcpy(st + 16, G.strip_start.data(), 4 * G.strip_start.size());
-            std::memcpy(st + 16 + 4 * G.strip_start.size(), G.strip_img.data(),
-                        4 * G.strip_img.size());
-        }
     }
     return DWT2_OK;
 }
@@ -1197,7 +1172,6 @@ int dwt2_forward_ex(const void *src, const dwt2_desc *src_d, void *coef, const d
         if (j >= k) {   // fused: parameters only (the kernel reads in of the first, ll of the last)
             tail.lv[j - k] = fwd_params(in, in_pitch, in_dt, w, h, ll, ll_pitch, ll_dt, hl, lh,
                                         hh, cp, T, wavelet, 0);
-            tail.lv[j - k].vec_in = word_rows(in, in_pitch, in_dt);
             continue;
         }
         if (head && j <= 2) {   // levels 1 and 2: one launch once both are planned
@@ -1286,9 +1260,6 @@ int dwt2_inverse_ex(const void *coef, const dwt2_desc *coef_d, void *dst, const 
             InvParams &p = tail.lv[levels - j];
             p = inv_params(ll, ll_pitch, ll_dt, hl, lh, hh, cp, T, out, out_pitch, out_dt, w, h,
                            wavelet, 0);
-            p.vec_ll = word_rows(ll, ll_pitch, ll_dt);
-            p.vec_band = word_rows(hl, cp, T) && word_rows(lh, cp, T) && word_rows(hh, cp, T);
-            p.vec_out = word_rows(out, out_pitch, out_dt);
             if (j > k) continue;
             const int F = levels + 1 - k;
             const TailPlan pl = plan_inv_tail(F, wavelet, tail.lv[0].nqx, tail.lv[0].nqy);
@@ -1403,24 +1374,18 @@ int dwt2_batch_run(const void *plan, size_t plan_bytes, const void *plan_device,
         const PlanLaunch &l = L[k];
         hipError_t e;
         if (l.tile == DWT2_TILE_HEAD) {
-            const size_t off = off_strips(l, h->inverse);
-            int32_t strips;
-            std::memcpy(&strips, static_cast<const char *>(plan) + off, sizeof strips);
-            const bool windows = strips == 0;
-            const int32_t *start = reinterpret_cast<const int32_t *>(
-                dev + (windows ? (size_t)l.off_start : off + 16));
-            const int32_t *img = windows ? reinterpret_cast<const int32_t *>(dev + l.off_img)
-                                         : start + l.images;
-            const int32_t tasks = windows ? l.total : strips;
+            const bool windows = head_plan_segment(plan, l, h->inverse) == 0;
+            const int32_t *img = reinterpret_cast<const int32_t *>(dev + l.off_img);
+            const int32_t *start = reinterpret_cast<const int32_t *>(dev + l.off_start);
             const char *prm = dev + l.off_params;
             if (h->inverse) {
                 const TableLaunch<InvHead> tl{img, start, reinterpret_cast<const InvHead *>(prm),
-                                              tasks};
+                                              l.total};
                 e = inv_head_plan_table(h->dtype)[h->wavelet][scheme][l.f32_a][l.f32_b](
                     tl, windows, any_odd_rows<InvHead>(plan, l), persistent, stream);
             } else {
                 const TableLaunch<FwdHead> tl{img, start, reinterpret_cast<const FwdHead *>(prm),
-                                              tasks};
+                                              l.total};
                 e = fwd_head_plan_table(h->dtype)[h->wavelet][scheme][l.f32_a][l.f32_b](
                     tl, windows, any_odd_rows<FwdHead>(plan, l), persistent, stream);
             }

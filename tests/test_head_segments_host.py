@@ -17,9 +17,8 @@ PARAMS = {0: 216, 1: 200}
 OWN, HALO = 48, 6
 
 
-def _head(sizes, dtype, wavelet, inverse, pad=0):
-    """(segment, 0 for windows, row pairs that a launch with it walks, and with 18)
-    of a plan of images whose rows are `pad` elements longer."""
+def _plan_of(sizes, dtype, wavelet, inverse, pad=0):
+    """The plan of one head launch of images whose rows are `pad` elements longer."""
     lib = _lib.load()
     es = 4 if dtype == _lib.F32 else 2
     arr = (_lib.Image * len(sizes))()
@@ -34,8 +33,14 @@ def _head(sizes, dtype, wavelet, inverse, pad=0):
     assert lib.dwt2_batch_plan_bytes(*args, ctypes.byref(n)) == 0
     buf = (ctypes.c_ubyte * n.value)()
     assert lib.dwt2_batch_plan(*args, buf, n.value) == 0
-    launches = HEADER.unpack_from(buf)[7]
-    assert launches == 1
+    assert HEADER.unpack_from(buf)[7] == 1
+    return bytes(buf)
+
+
+def _head(sizes, dtype, wavelet, inverse, pad=0):
+    """(segment, 0 for windows, row pairs that a launch with it walks, and with 18)
+    of a plan of images whose rows are `pad` elements longer."""
+    buf = _plan_of(sizes, dtype, wavelet, inverse, pad)
     off = LAUNCH.unpack_from(buf, HEADER.size)[8]
     seg = struct.unpack_from("<i", buf, off + PARAMS[inverse] - 4)[0]
 
@@ -87,3 +92,24 @@ def test_windows_or_strips(wavelet, dtype, inverse, windows, strips):
     for per_cu in windows + strips:
         seg = _head([(232, int(per_cu * cus) * rows)], dtype, wavelet, inverse)[0]
         assert (seg == 0) == (per_cu in windows), per_cu
+
+
+@pytest.mark.parametrize("inverse", [0, 1])
+@pytest.mark.parametrize("dtype", [_lib.F32, _lib.F16])
+@pytest.mark.parametrize("sizes", [[(4096, 4096), (64, 96), (196, 52)], [(64, 64)] * 9])
+def test_a_plan_holds_the_map_of_the_layout_that_runs(sizes, dtype, inverse):
+    """And no other: its tasks, image by image, are all that its bytes hold
+    beside the parameters."""
+    plan = _plan_of(sizes, dtype, 0, inverse)
+    images, total, img, start, params = LAUNCH.unpack_from(plan, HEADER.size)[4:]
+    seg = struct.unpack_from("<i", plan, params + PARAMS[inverse] - 4)[0]
+    tall = 22 if inverse else 18
+    counts = [-(-(w // 4) // (OWN if seg else 58)) * -(-(h // 4) // (seg or tall))
+              for w, h in sizes]
+    assert images == len(sizes) and total == sum(counts)
+    starts = [sum(counts[:i]) for i in range(images)]
+    assert list(struct.unpack_from(f"<{images}i", plan, start)) == starts
+    assert list(struct.unpack_from(f"<{total}i", plan, img)) == [
+        i for i, c in enumerate(counts) for _ in range(c)]
+    assert len(plan) <= HEADER.size + LAUNCH.size + 4 * (total + images) + \
+        PARAMS[inverse] * images + 5 * 256
