@@ -335,6 +335,7 @@ TailPlan plan_inv_tail(int F, int wavelet, int nqx_first, int nqy_first) {
 // 16-bit 229 with 18 (9: 253).
 struct HeadShape {
     int nqx, nqy;   // level j+1 quads
+    bool odd;       // odd_rows of the image
 };
 int64_t head_tasks(const HeadShape *im, int n, int seg) {
     int64_t t = 0;
@@ -421,12 +422,16 @@ int64_t head_windows(const HeadShape &im, bool inverse) {
 //     18.3 (23.5, 21.7)
 //   5/3 inverse 490: 13.4, 19.3 (16.3, 21.6); 846: 21.6, 22.8 (26.4, 27.6); 1260: 28.5,
 //     28.2 (36.5, 36.1)
-bool head_by_windows(const HeadShape *im, int n, int wavelet, bool wide, bool inverse, bool odd,
+// A launch of several images is taken for what most of its windows are.
+bool head_by_windows(const HeadShape *im, int n, int wavelet, bool wide, bool inverse,
                      bool off_sectors) {
     const int64_t cus = device_cus();
-    int64_t w = 0;
-    for (int i = 0; i < n; ++i) w += head_windows(im[i], inverse);
-    if (odd) return 2 * w <= cus * (wavelet == DWT2_CDF97 ? 16 : inverse ? 8 : 5);
+    int64_t w = 0, odd = 0;
+    for (int i = 0; i < n; ++i) {
+        w += head_windows(im[i], inverse);
+        if (im[i].odd) odd += head_windows(im[i], inverse);
+    }
+    if (2 * odd > w) return 2 * w <= cus * (wavelet == DWT2_CDF97 ? 16 : inverse ? 8 : 5);
     if (wavelet == DWT2_CDF97 && wide && !inverse && off_sectors && w > 6 * cus) return true;
     if (wavelet == DWT2_CDF97) return 2 * w <= cus * (wide ? 4 : inverse ? 8 : 9);
     if (!inverse) return false;
@@ -439,13 +444,10 @@ bool head_off_sectors(const FwdHead &h) {
     return (((uintptr_t)h.l1.hl | (uintptr_t)h.l1.lh | (uintptr_t)h.l1.hh | pitch) & 63) != 0;
 }
 bool head_off_sectors(const InvHead &) { return false; }
-// The rows per segment of a head launch, or 0 where it runs by windows. odd:
-// odd_rows of any of the launch's images (all of them then run the kernel for
-// such rows: 32 FP16 images of sides up to 4096, one level, 26.8 us forward with
-// one odd image among them as without).
-int head_layout(const HeadShape *im, int n, int wavelet, bool wide, bool inverse, bool odd,
+// The rows per segment of a head launch, or 0 where it runs by windows.
+int head_layout(const HeadShape *im, int n, int wavelet, bool wide, bool inverse,
                 bool streamed = false, bool off_sectors = false) {
-    return head_by_windows(im, n, wavelet, wide, inverse, odd, off_sectors)
+    return head_by_windows(im, n, wavelet, wide, inverse, off_sectors)
                ? 0 : head_segment(im, n, wavelet, wide, inverse, streamed);
 }
 
@@ -456,14 +458,14 @@ int head_grid(H &hd, int seg) {
     constexpr int X = HeadWindow::FOX2;
     hd.seg = seg;
     hd.across = seg ? (hd.l2.nqx + kHeadOwn - 1) / kHeadOwn : (hd.l2.nqx + X - 1) / X;
-    const HeadShape im{hd.l2.nqx, hd.l2.nqy};
+    const HeadShape im{hd.l2.nqx, hd.l2.nqy, false};
     return (int)(seg ? head_tasks(&im, 1, seg) : head_windows(im, std::is_same<H, InvHead>::value));
 }
 template <typename H>
 int head_grid_one(H &hd, int wavelet, int dt, bool inverse, bool streamed) {
-    const HeadShape im{hd.l2.nqx, hd.l2.nqy};
-    return head_grid(hd, head_layout(&im, 1, wavelet, dt == DWT2_F32, inverse, odd_rows(hd),
-                                     streamed, head_off_sectors(hd)));
+    const HeadShape im{hd.l2.nqx, hd.l2.nqy, odd_rows(hd)};
+    return head_grid(hd, head_layout(&im, 1, wavelet, dt == DWT2_F32, inverse, streamed,
+                                     head_off_sectors(hd)));
 }
 
 // Size class of a level whose input is width x height pixels.
@@ -796,8 +798,6 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
         G.l.f32_a = inverse ? ll2_f32 : dtype == DWT2_F32;
         G.l.f32_b = inverse ? dtype == DWT2_F32 : ll2_f32;
         std::vector<HeadShape> shapes(n);
-        for (int i = 0; i < n; ++i) shapes[i] = {images[i].width / 4, images[i].height / 4};
-        bool odd = false;
         for (int i = 0; i < n; ++i) {
             const dwt2_image &im = images[i];
             const int W = im.width, H = im.height;
@@ -816,7 +816,7 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
                                    cb + (size_t)((int64_t)(H / 2) * cp) * es,
                                    cb + (size_t)((int64_t)(H / 2) * cp + W / 2) * es, cp, dtype,
                                    im.dst, im.dst_pitch, dtype, W, H, wavelet, 0);
-                odd |= odd_rows(hd);
+                shapes[i] = {W / 4, H / 4, odd_rows(hd)};
                 G.ih.push_back(hd);
             } else {
                 char *cb = static_cast<char *>(im.dst);
@@ -832,13 +832,13 @@ int build_plan(const dwt2_image *images, int32_t n, int32_t dtype, int32_t wavel
                                    cb + (size_t)((int64_t)(H / 4) * cp) * es,
                                    cb + (size_t)((int64_t)(H / 4) * cp + W / 4) * es, cp, dtype,
                                    wavelet, 0);
-                odd |= odd_rows(hd);
+                shapes[i] = {W / 4, H / 4, odd_rows(hd)};
                 G.fh.push_back(hd);
             }
         }
         // one layout and segment height for the launch: its workgroups hold
         // strips of several images
-        const int seg = head_layout(shapes.data(), n, wavelet, dtype == DWT2_F32, inverse, odd);
+        const int seg = head_layout(shapes.data(), n, wavelet, dtype == DWT2_F32, inverse);
         if (seg && head_tasks(shapes.data(), n, seg) > (int64_t)INT32_MAX - kHeadWaves)
             return DWT2_ERR_INVALID_ARG;
         for (int i = 0; i < n; ++i) {
@@ -1595,17 +1595,14 @@ int head_batch(const dwt2_level_job *jobs, int32_t n, int32_t wavelet, int32_t s
                                        c.ll, c.ll_pitch, c.ll_dtype, c.hl, c.lh, c.hh,
                                        c.band_pitch, c.band_dtype, wavelet, 0);
                 }
-                shapes[b.n] = {c.width / 2, c.height / 2};
+                shapes[b.n] = {c.width / 2, c.height / 2, odd_rows(b.h[b.n])};
                 ++b.n;
                 done[i] = true;
             }
             if (b.n > 0 && (b.n == kHeadBatchMax || i == n)) {
                 // one layout and segment height for the launch: its workgroups
                 // hold strips of several images
-                bool odd = false;
-                for (int k = 0; k < b.n; ++k) odd |= odd_rows(b.h[k]);
-                const int seg =
-                    head_layout(shapes, b.n, wavelet, key.band_dt == DWT2_F32, INV, odd);
+                const int seg = head_layout(shapes, b.n, wavelet, key.band_dt == DWT2_F32, INV);
                 if (seg && head_tasks(shapes, b.n, seg) > (int64_t)INT32_MAX - kHeadWaves) {
                     st = DWT2_ERR_INVALID_ARG;
                     break;

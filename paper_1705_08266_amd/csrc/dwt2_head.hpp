@@ -77,8 +77,8 @@ struct InvHead {
 
 // Whether pixel or level j band rows may start at the upper half of a word (level
 // j+1 is accessed one element at a time).
-inline bool odd_rows(const FwdHead &h) { return !(h.l1.vec_in && h.l1.vec_band); }
-inline bool odd_rows(const InvHead &h) { return !(h.l1.vec_band && h.l1.vec_out); }
+__host__ __device__ inline bool odd_rows(const FwdHead &h) { return !(h.l1.vec_in && h.l1.vec_band); }
+__host__ __device__ inline bool odd_rows(const InvHead &h) { return !(h.l1.vec_band && h.l1.vec_out); }
 
 // One strip's segment, forward: rows o..o+seg of level j+1, the window's first
 // lane at column wx. EX, EY: the window reaches the left or right (upper or

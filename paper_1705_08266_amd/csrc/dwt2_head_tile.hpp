@@ -340,6 +340,25 @@ __device__ __forceinline__ void inv_head_tile(const InvHead &hd, const int t,
     }
 }
 
+// A window of one image of several. ODD: the launch has images whose rows may
+// start at odd halves; the others take the word path in it all the same.
+template <int WV, int SCH, int ROWS, int WAVES, typename TIN, typename TLL, typename TB, bool ODD>
+__device__ __forceinline__ void fwd_image_window(const FwdHead &hd, const int t,
+                                                 FwdTileLds<ROWS, WAVES> &lds) {
+    if (ODD && odd_rows(hd))   // workgroup-uniform
+        fwd_head_tile<WV, SCH, ROWS, WAVES, TIN, TLL, TB, ODD>(hd, t, lds);
+    else
+        fwd_head_tile<WV, SCH, ROWS, WAVES, TIN, TLL, TB, false>(hd, t, lds);
+}
+template <int WV, int SCH, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT, bool ODD>
+__device__ __forceinline__ void inv_image_window(const InvHead &hd, const int t,
+                                                 InvTileLds<ROWS, WAVES> &lds) {
+    if (ODD && odd_rows(hd))   // workgroup-uniform
+        inv_head_tile<WV, SCH, ROWS, WAVES, TLL, TB, TOUT, ODD>(hd, t, lds);
+    else
+        inv_head_tile<WV, SCH, ROWS, WAVES, TLL, TB, TOUT, false>(hd, t, lds);
+}
+
 // One workgroup per tile of one image.
 template <int WV, int SCH, int ROWS, int WAVES, typename TIN, typename TLL, typename TB, bool ODD>
 __global__ __launch_bounds__(64 * WAVES, (kFwdHeadWavesPerSimd<SCH, WAVES, TIN>)) void fwd_head_tile_kernel(
@@ -366,7 +385,7 @@ __global__ __launch_bounds__(64 * WAVES, kTableHeadWavesPerSimd<WAVES>) void fwd
     for (int t = block_tile(); t < tl.total; t += gridDim.x) {
         const int i = load_uniform(tl.img + t);
         const FwdHead hd = load_uniform(tl.params + i);
-        fwd_head_tile<WV, SCH, ROWS, WAVES, TIN, TLL, TB, ODD>(hd, t - load_uniform(tl.start + i), lds);
+        fwd_image_window<WV, SCH, ROWS, WAVES, TIN, TLL, TB, ODD>(hd, t - load_uniform(tl.start + i), lds);
         __syncthreads();
     }
 }
@@ -378,7 +397,7 @@ __global__ __launch_bounds__(64 * WAVES, kTableHeadWavesPerSimd<WAVES>) void inv
     for (int t = block_tile(); t < tl.total; t += gridDim.x) {
         const int i = load_uniform(tl.img + t);
         const InvHead hd = load_uniform(tl.params + i);
-        inv_head_tile<WV, SCH, ROWS, WAVES, TLL, TB, TOUT, ODD>(hd, t - load_uniform(tl.start + i), lds);
+        inv_image_window<WV, SCH, ROWS, WAVES, TLL, TB, TOUT, ODD>(hd, t - load_uniform(tl.start + i), lds);
         __syncthreads();
     }
 }
@@ -390,7 +409,7 @@ __global__ __launch_bounds__(64 * WAVES, kTableHeadWavesPerSimd<WAVES>) void fwd
     __shared__ FwdTileLds<ROWS, WAVES> lds;
     const int t = block_tile();
     const int i = batch_image(bt, t);
-    fwd_head_tile<WV, SCH, ROWS, WAVES, TIN, TLL, TB, ODD>(bt.h[i], t - bt.tile_start[i], lds);
+    fwd_image_window<WV, SCH, ROWS, WAVES, TIN, TLL, TB, ODD>(bt.h[i], t - bt.tile_start[i], lds);
 }
 
 template <int WV, int SCH, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT, bool ODD>
@@ -399,7 +418,7 @@ __global__ __launch_bounds__(64 * WAVES, kTableHeadWavesPerSimd<WAVES>) void inv
     __shared__ InvTileLds<ROWS, WAVES> lds;
     const int t = block_tile();
     const int i = batch_image(bt, t);
-    inv_head_tile<WV, SCH, ROWS, WAVES, TLL, TB, TOUT, ODD>(bt.h[i], t - bt.tile_start[i], lds);
+    inv_image_window<WV, SCH, ROWS, WAVES, TLL, TB, TOUT, ODD>(bt.h[i], t - bt.tile_start[i], lds);
 }
 
 }  // namespace dwt2

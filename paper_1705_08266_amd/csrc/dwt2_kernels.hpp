@@ -43,8 +43,8 @@ struct InvParams {
 // kernels with ODD set take (RowIn, store_cols): kernels of their own, since
 // in one with the word path their registers cost it wavefronts (4096^2 FP16
 // forward: 16.5 us alone, 18.4 with both).
-inline bool odd_rows(const FwdParams &p) { return !(p.vec_in && p.vec_ll && p.vec_band); }
-inline bool odd_rows(const InvParams &p) { return !(p.vec_ll && p.vec_band && p.vec_out); }
+__host__ __device__ inline bool odd_rows(const FwdParams &p) { return !(p.vec_in && p.vec_ll && p.vec_band); }
+__host__ __device__ inline bool odd_rows(const InvParams &p) { return !(p.vec_ll && p.vec_band && p.vec_out); }
 
 // Geometry of a tile configuration. The horizontal halo is one lane's worth
 // of quads on each side (>= the number of lifting pairs), which keeps every
@@ -428,6 +428,27 @@ __global__ __launch_bounds__(64 * WAVES) void inv_level_kernel(InvParams prm) {
     inv_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT, ODD>(prm, block_tile(), box, lane, wave);
 }
 
+// A tile of one image of several. ODD: the launch has images whose rows may start
+// at odd halves; the others take the word path in it all the same.
+template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TIN, typename TLL, typename TB,
+          bool ODD>
+__device__ __forceinline__ void fwd_image_tile(const FwdParams &prm, int t,
+                                               Mailbox<QPL, WAVES> &box, int lane, int wave) {
+    if (ODD && odd_rows(prm))   // workgroup-uniform
+        fwd_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB, ODD>(prm, t, box, lane, wave);
+    else
+        fwd_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB, false>(prm, t, box, lane, wave);
+}
+template <int WV, int SCH, int QPL, int ROWS, int WAVES, typename TLL, typename TB, typename TOUT,
+          bool ODD>
+__device__ __forceinline__ void inv_image_tile(const InvParams &prm, int t,
+                                               Mailbox<QPL, WAVES> &box, int lane, int wave) {
+    if (ODD && odd_rows(prm))   // workgroup-uniform
+        inv_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT, ODD>(prm, t, box, lane, wave);
+    else
+        inv_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT, false>(prm, t, box, lane, wave);
+}
+
 // ---- single levels of many images, parameters in the kernel arguments -----------
 // Up to kBatchMax level jobs of one size class per launch (continuous
 // batching: a different set of jobs every call, so nothing is planned ahead);
@@ -468,8 +489,8 @@ __global__ __launch_bounds__(64 * WAVES) void fwd_batch_kernel(FwdBatch bt) {
     const int total = bt.tile_start[bt.n];
     for (int t = block_tile(); t < total; t += gridDim.x) {
         const int i = batch_image(bt, t);
-        fwd_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB, ODD>(bt.p[i], t - bt.tile_start[i], box, lane,
-                                                          wave);
+        fwd_image_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB, ODD>(
+            bt.p[i], t - bt.tile_start[i], box, lane, wave);
     }
 }
 
@@ -482,8 +503,8 @@ __global__ __launch_bounds__(64 * WAVES) void inv_batch_kernel(InvBatch bt) {
     const int total = bt.tile_start[bt.n];
     for (int t = block_tile(); t < total; t += gridDim.x) {
         const int i = batch_image(bt, t);
-        inv_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT, ODD>(bt.p[i], t - bt.tile_start[i], box, lane,
-                                                           wave);
+        inv_image_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT, ODD>(
+            bt.p[i], t - bt.tile_start[i], box, lane, wave);
     }
 }
 
@@ -533,8 +554,8 @@ __global__ __launch_bounds__(64 * WAVES) void fwd_table_kernel(TableLaunch<FwdPa
     for (int t = block_tile(); t < tl.total; t += gridDim.x) {
         const int i = load_uniform(tl.img + t);
         const FwdParams prm = load_uniform(tl.params + i);
-        fwd_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB, ODD>(prm, t - load_uniform(tl.start + i), box,
-                                                               lane, wave);
+        fwd_image_tile<WV, SCH, QPL, ROWS, WAVES, TIN, TLL, TB, ODD>(
+            prm, t - load_uniform(tl.start + i), box, lane, wave);
     }
 }
 
@@ -547,8 +568,8 @@ __global__ __launch_bounds__(64 * WAVES) void inv_table_kernel(TableLaunch<InvPa
     for (int t = block_tile(); t < tl.total; t += gridDim.x) {
         const int i = load_uniform(tl.img + t);
         const InvParams prm = load_uniform(tl.params + i);
-        inv_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT, ODD>(prm, t - load_uniform(tl.start + i), box,
-                                                               lane, wave);
+        inv_image_tile<WV, SCH, QPL, ROWS, WAVES, TLL, TB, TOUT, ODD>(
+            prm, t - load_uniform(tl.start + i), box, lane, wave);
     }
 }
 
