@@ -80,6 +80,16 @@ struct InvHead {
 __host__ __device__ inline bool odd_rows(const FwdHead &h) { return !(h.l1.vec_in && h.l1.vec_band); }
 __host__ __device__ inline bool odd_rows(const InvHead &h) { return !(h.l1.vec_band && h.l1.vec_out); }
 
+// A wavefront-uniform value that the compiler takes for another than v. The row
+// loops end at the last row that is loaded; knowing that, it drops the test of
+// each first load of a group and schedules the loop anew, in 130 registers
+// instead of 112 (FP32 9/7 inverse: three wavefronts to a SIMD) and 114 instead of
+// 106 (forward: 4096^2 34.2 us, not 33.1).
+__device__ __forceinline__ int opaque(int v) {
+    asm("" : "+s"(v));
+    return v;
+}
+
 // One strip's segment, forward: rows o..o+seg of level j+1, the window's first
 // lane at column wx. EX, EY: the window reaches the left or right (upper or
 // lower) edge of the image. MODE: how rows are addressed.
@@ -108,7 +118,7 @@ __device__ __forceinline__ void fwd_head_strip(const FwdHead &hd, const int wx, 
     const int lane = threadIdx.x & 63;
     const int X = wx + lane;                              // the lane's level j+1 column
     const int e = min(o + hd.seg, p2.nqy);
-    const int t0 = o - G::F0, t1 = e + G::F1;
+    const int t0 = o - G::F0, t1 = e + G::F1, tl = opaque(t1);
     const ColMarks m{X == 0, X == p2.nqx - 1};
     const bool own = lane >= G::HALO && lane < G::HALO + OWN && X < p2.nqx;
     const uint32_t offi = 4u * (uint32_t)min(max(X, 0), p2.nqx - 1) * (uint32_t)sizeof(TIN);
@@ -144,7 +154,7 @@ __device__ __forceinline__ void fwd_head_strip(const FwdHead &hd, const int wx, 
         fetch(t0 + i, raw[i]);
         pad_stores((KEEP && i + 1 == AHEAD) ? 7 : 10);
     }
-    for (int tb = t0; tb <= t1; tb += D) {
+    for (int tb = t0; tb <= tl; tb += D) {
 #pragma unroll
         for (int i = 0; i < D; ++i) {
             const int t = tb + i;
@@ -224,7 +234,7 @@ __device__ __forceinline__ void inv_head_strip(const InvHead &hd, const int wx, 
     const int lane = threadIdx.x & 63;
     const int X = wx + lane;
     const int e = min(o + hd.seg, p2.nqy);
-    const int t0 = o - G::I0, t1 = e + G::I1;
+    const int t0 = o - G::I0, t1 = e + G::I1, tl = opaque(t1);
     const ColMarks m{X == 0, X == p2.nqx - 1};
     const bool own = lane >= G::HALO && lane < G::HALO + OWN && X < p2.nqx;
     const uint32_t Xc = (uint32_t)min(max(X, 0), p2.nqx - 1);
@@ -274,7 +284,7 @@ __device__ __forceinline__ void inv_head_strip(const InvHead &hd, const int wx, 
         fetch(t0 + i, raw[i]);
         pad_stores(4);
     }
-    for (int tb = t0; tb <= t1; tb += D) {
+    for (int tb = t0; tb <= tl; tb += D) {
 #pragma unroll
         for (int i = 0; i < D; ++i) {
             const int t = tb + i;
