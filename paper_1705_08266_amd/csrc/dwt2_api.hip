@@ -324,15 +324,19 @@ TailPlan plan_inv_tail(int F, int wavelet, int nqx_first, int nqy_first) {
 // has at most c per CU, if there is one (a launch of many small images has more
 // strips than that at any height), is weighed at the time its row pairs take:
 // measured 0.97, 1.8, 2.85, 3.5 us each with c = 1, 2, 3, 4 workgroups on a CU
-// in FP32, 0.83, 1.23, 1.75, 2.3 with 16-bit storage, whatever the image, and
-// beyond four, which is what fits on a CU, in proportion (FP32 with
-// streamed output 1.7 at c = 2: 5504^2 inverse 53.0 us against 57.9 at c = 1). Forward, us
-// with c = 1, 2, 3, 4: FP32 2048^2 12.8, 14.6 and 7680x4320 56.1, 60.0, 62.5,
-// 63.3; 16-bit 2048^2 12.5, 13.4, 4096^2 27.7, 25.1, 27.7 and 7680x4320 47.5,
-// 40.2, 39.7, 44.3. With eight or more workgroups per CU the grid evens out by
-// itself, and short segments keep the rows in flight together: 16384^2 FP32
-// forward 426 us with 9 rows (12: 436, 36: 450), inverse 445 with 15 (9: 453),
-// 16-bit 229 with 18 (9: 253).
+// in FP32 (9/7 forward 1.0, 2.1, 3.1, 4.0: a second workgroup gives it nothing),
+// 0.83, 1.23, 1.75, 2.3 with 16-bit storage, whatever the image, and beyond four,
+// which is what fits on a CU, in proportion (FP32 with streamed output 1.7 at
+// c = 2: 5504^2 inverse 54.9 us against 59.7 at c = 1). Forward, us with c = 1, 2,
+// 3, 4: FP32 2048^2 12.9, 14.6, 7680x4320 60.0, 61.3, 64.8, 66.2, 8192^2 101, 112,
+// 115, 120; 16-bit 4096x8192 44.5, 37.4, 37.6, 39.5.
+// Of the 5/3, short segments keep the rows in flight together where the grid evens
+// out by itself: from 12 workgroups per CU on, us with those and with the segment
+// weighed best: FP32 forward 6144 x 16384 159, 164; 12288^2 235, 242; 16384^2 391,
+// 405; 16-bit forward 14336^2 179, 186; 16384^2 217, 221; inverse 162, 169 and 203,
+// 207; but FP32 inverse 16384^2 401, 392. The 9/7 never gain: 16384^2 FP32 forward
+// 411, 405, inverse 408, 381; 16-bit 227, 229 and 217, 216. Launches of several
+// images, whose heights differ, take the short ones from 8 per CU on.
 struct HeadShape {
     int nqx, nqy;   // level j+1 quads
     bool odd;       // odd_rows of the image
@@ -345,11 +349,15 @@ int64_t head_tasks(const HeadShape *im, int n, int seg) {
 }
 int head_segment(const HeadShape *im, int n, int wavelet, bool wide, bool inverse,
                  bool streamed) {
-    static const double kPairTime[2][4] = {{0.83, 1.23, 1.75, 2.3}, {0.97, 1.8, 2.85, 3.5}};
+    static const double kPairTime[3][4] = {
+        {0.83, 1.23, 1.75, 2.3}, {0.97, 1.8, 2.85, 3.5}, {1.0, 2.1, 3.1, 4.0}};
+    const bool fwd97 = wide && !inverse && wavelet == DWT2_CDF97;
+    const double *pair_time = kPairTime[fwd97 ? 2 : wide];
     const double kPairTimeStream2 = 1.7;
     const int64_t cus = device_cus();
     const int many = !wide ? 18 : inverse ? 15 : 9;
-    if (head_tasks(im, n, many) >= 8 * kHeadWaves * cus) return many;
+    const int even = n > 1 ? 8 : wavelet == DWT2_CDF53 && !(wide && inverse) ? 12 : 0;
+    if (even && head_tasks(im, n, many) >= even * kHeadWaves * cus) return many;
     const int halo = wavelet == DWT2_CDF97 ? 6 : 4, D = kHeadDepth;
     int tallest = 1;
     for (int i = 0; i < n; ++i) tallest = std::max(tallest, im[i].nqy);
@@ -363,9 +371,9 @@ int head_segment(const HeadShape *im, int n, int wavelet, bool wide, bool invers
         }
         if (head_tasks(im, n, lo) > c * kHeadWaves * cus) continue;   // none has
         const int pairs = (lo + halo + D - 1) / D * D;   // whole groups of D
-        const double time = c > 4 ? kPairTime[wide][3] * c / 4
-                            : wide && streamed && c == 2 ? kPairTimeStream2
-                                                         : kPairTime[wide][c - 1];
+        const double time = c > 4 ? pair_time[3] * c / 4
+                            : wide && !fwd97 && streamed && c == 2 ? kPairTimeStream2
+                                                                   : pair_time[c - 1];
         if (best == 0 || pairs * time < best) {
             best = pairs * time;
             seg = std::min(pairs - halo, tallest);
@@ -395,7 +403,8 @@ int64_t head_windows(const HeadShape &im, bool inverse) {
 //     18.2, 19.7 (21.2, 22.9); 552: 22.7, 19.9 (26.0, 24.3)
 //   9/7 inverse 16-bit: 216: 9.6, 13.3 (10.8, 13.6); 600: 17.8, 20.2 (20.8, 21.5); 930:
 //     21.6, 26.8 (27.0, 28.7); 1056: 25.8, 26.6 (31.2, 29.0); with streamed pixels, 930:
-//     20.3, 25.6 (25.0, 27.0); 1056: 24.0, 25.6 (28.7, 27.1)
+//     20.3, 25.6 (25.0, 27.0); 1081: 23.3, 25.2 (27.4, 27.0); 1320: 29.1, 32.7 (33.9,
+//     33.8); 1357: 27.5, 28.9 (33.2, 31.1)
 // The 5/3 strips carry half the stages and less halo. Forward they are faster at
 // every size (see kFwdByWindows); inverse, windows are where most of a round of
 // them is resident, one to a CU or two (FP32, whose rounds take longer: only
@@ -433,7 +442,7 @@ bool head_by_windows(const HeadShape *im, int n, int wavelet, bool wide, bool in
     }
     if (2 * odd > w) return 2 * w <= cus * (wavelet == DWT2_CDF97 ? 16 : inverse ? 8 : 5);
     if (wavelet == DWT2_CDF97 && wide && !inverse && off_sectors && w > 6 * cus) return true;
-    if (wavelet == DWT2_CDF97) return 2 * w <= cus * (wide ? 4 : inverse ? 8 : 9);
+    if (wavelet == DWT2_CDF97) return 4 * w <= cus * (wide ? 8 : inverse ? 21 : 18);
     if (!inverse) return false;
     if (!wide) return 8 * w > 3 * cus && w <= 2 * cus;
     return (4 * w > 3 * cus && w <= cus) || (2 * w > 3 * cus && w <= 2 * cus);
