@@ -136,9 +136,10 @@ int dwt2_forward(const void *src, const dwt2_desc *src_d, void *coef, const dwt2
  * order with negated coefficients (Sec. 2 and 3 define the forward steps; the
  * paper does not spell out the inverse). Arguments as for dwt2_forward. When
  * dst holds 32 MiB or more (one launch per level: up to 256 MiB), the finest
- * level writes it with non-temporal stores, as the fused head of the forward
- * does the bands of a pyramid of more than 256 MiB (the values are the same;
- * the lines are not kept in the GPU caches). */
+ * level writes it with non-temporal stores, as a fused head of the forward that
+ * runs by strips does the bands of a pyramid of more than 256 MiB
+ * (dwt2_head_layout; the values are the same, the lines are not kept in the GPU
+ * caches). */
 int dwt2_inverse(const void *coef, const dwt2_desc *coef_d, void *dst, const dwt2_desc *dst_d,
                  dwt2_wavelet wavelet, int32_t levels, dwt2_boundary boundary,
                  dwt2_scheme scheme, void *workspace, size_t workspace_bytes,
@@ -204,9 +205,9 @@ int dwt2_head_layout(const void *src, const dwt2_desc *src_d, const void *dst,
  *           DWT2_TILE_TAIL for each of the last 2..DWT2_TAIL_MAX levels:
  *           those run fused in one launch (one workgroup computes every
  *           fused level for its block; intermediate low-low bands stay in
- *           LDS), or DWT2_TILE_HEAD for both levels 1 and 2 (fused the same
- *           way; the tail must then start at level 3 or later). Entry j
- *           belongs to level j+1.
+ *           LDS), or DWT2_TILE_HEAD for both levels 1 and 2 (fused into one
+ *           launch, see dwt2_head_layout; the tail must then start at level 3
+ *           or later). Entry j belongs to level j+1.
  *   level_events : NULL, or 2*levels events; events [2j] and [2j+1] are
  *           recorded on `stream` before and after the launch of level j+1.
  *           For fused tail levels the first fused level's pair brackets the

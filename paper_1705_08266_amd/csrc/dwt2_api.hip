@@ -1513,8 +1513,9 @@ int level_batch(const dwt2_level_job *jobs, int32_t n, int32_t wavelet, int32_t 
 
 // Head level batches: jobs[2i] is the finer level j and jobs[2i+1] the
 // coarser level j+1 of pair i, each a level job as in the level batches. The
-// band between them (the finer job's ll, the coarser job's full) stays in LDS
-// in FP32 and is not accessed, so it must be that one FP32 buffer.
+// band between them (the finer job's ll, the coarser job's full) stays in FP32
+// on chip (registers or LDS) and is not accessed, so it must be that one FP32
+// buffer.
 struct HeadKey {
     int band_dt, a_f32, b_f32;
     bool operator==(const HeadKey &o) const {

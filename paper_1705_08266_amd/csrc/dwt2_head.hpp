@@ -15,11 +15,12 @@
 // What bounds it. The bytes: a strip reads its pixels and writes its bands
 // once, plus the halo (6 quads of level j on each side of what it owns). Three
 // things decide how close the launch comes to the copy rate:
-//   - whole lines. A strip owns OWN = 48 of its 64 lanes, so every row piece it
-//     writes starts on a line: FP32 bands of level j in pieces of 384 bytes,
-//     pixels in 768. The halo lanes this gives up cost reads that L2 answers;
-//     pieces of 58 lanes (all that the halo leaves) share a line at both ends
-//     with the next strip's, and lines that L2 evicts half written go out
+//   - whole lines. A strip owns OWN = 48 of its 64 lanes. So pixels and the FP32
+//     bands of level j are written in pieces of 768 and 384 bytes that start on
+//     a line, where the rows do; the other pieces (192 bytes, or 96) start on
+//     half a line or a quarter. The halo lanes this gives up cost reads that L2
+//     answers; pieces of 58 lanes (all that the halo leaves) share a line at both
+//     ends with the next strip's, and lines that L2 evicts half written go out
 //     twice: 16384^2 FP32 forward 486 us with 58 lanes, 443 with 48 (segments
 //     of 18).
 //   - lockstep. The wavefronts of a workgroup are neighbouring strips; a barrier
@@ -28,12 +29,13 @@
 //     long: 463 -> 443 us at the same shape.
 //   - loads far ahead. The next D - 1 row pairs are in flight while one is
 //     lifted.
-// Before, a workgroup of 12 wavefronts lifted a 128 x 48-quad window in
-// registers with the low-low band in LDS: 47% more lifting and loads than
-// owned quads, ten barriers per window, loads, lifting and stores one after
-// the other (16384^2 forward: 474 us FP32, 285 us FP16; now 399 and 225, against
-// 421 and 211 for the bytes at the 5.1 TB/s of a plain copy; 4096^2 FP32 forward
-// 37.3 -> 31.7, inverse 29.0 -> 26.6 with its bands in the Infinity Cache).
+// By windows (dwt2_head_tile.hpp), which ran everything before, a workgroup of 12
+// wavefronts lifts a 128 x 48-quad window with the low-low band in LDS: 47% more
+// lifting and loads than owned quads, ten barriers per window, loads, lifting
+// and stores one after the other. 16384^2 forward: 474 us FP32, 285 FP16; by
+// strips 405 and 229, for bytes that the 6.2 TB/s of a large copy moves in 346 and
+// 173; 4096^2 FP32 forward 37.6 -> 33.3, inverse 29.1 -> 27.2 with its bands in the
+// Infinity Cache.
 #pragma once
 
 #include <type_traits>

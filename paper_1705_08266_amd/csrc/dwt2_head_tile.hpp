@@ -69,17 +69,15 @@ __device__ __forceinline__ int lds_at(int p, int p0, int n) { return min(max(p -
 
 // Wavefronts per SIMD that the register allocation must allow. Two head
 // workgroups share a CU (their LDS fits twice), which takes WAVES/2 per SIMD,
-// i.e. at most 80 VGPRs for 12 wavefronts. Left free, forward heads with
-// 16-bit input come out at 80-81 (the separable FP16 one and the BF16 ones at
-// 81) and then run one workgroup per CU (about 35% slower); those
-// instantiations are held to the budget. The FP32 ones fit as they are and
-// keep the allocation the workgroup size alone implies.
+// i.e. at most 80 VGPRs for 12 wavefronts; with 81 one runs on a CU, about 35%
+// slower. Left free, forward heads of BF16 rows that may start at odd halves come
+// out at 87 (held to the budget 80 and 8-16 bytes spilled), all others at 56-80.
 template <int SCH, int WAVES, typename TIN>
 constexpr int kFwdHeadWavesPerSimd = sizeof(TIN) == 2 ? (2 * WAVES + 3) / 4 : (WAVES + 3) / 4;
 template <int WAVES>
 constexpr int kInvHeadWavesPerSimd = (WAVES + 3) / 4;
-// The batched heads (which read their parameters from the plan, one more
-// register or so) are all held to the two-workgroup budget.
+// The planned heads (which read their parameters from memory, one more register
+// or so) are all held to the two-workgroup budget.
 template <int WAVES>
 constexpr int kTableHeadWavesPerSimd = (2 * WAVES + 3) / 4;
 

@@ -6,7 +6,8 @@
 // waits for the row below it (T_P reads the lower neighbours) and what S_U
 // needs of the row above; pushing row r in emits row r - 1 finished. Stages
 // follow each other without leaving the registers, so a row is read once,
-// nothing goes through LDS and no wavefront waits for another.
+// nothing goes through LDS and no wavefront needs another's data (the barrier
+// per row pair that the sweeps pass only keeps neighbouring strips together).
 //
 // Arithmetic per quad is that of the register-tile steps (dwt2_device.hpp),
 // term by term, so the results are the same bits.
