@@ -330,12 +330,13 @@ TailPlan plan_inv_tail(int F, int wavelet, int nqx_first, int nqy_first) {
 // c = 2: 5504^2 inverse 54.9 us against 59.7 at c = 1). Forward, us with c = 1, 2,
 // 3, 4: FP32 2048^2 12.9, 14.6, 7680x4320 60.0, 61.3, 64.8, 66.2, 8192^2 101, 112,
 // 115, 120; 16-bit 4096x8192 44.5, 37.4, 37.6, 39.5.
-// Of 5/3 launches and 16-bit forwards, short segments keep the rows in flight
-// together where the grid evens out by itself: from 12 workgroups per CU on, us
-// with those and with the segment weighed best: 5/3 FP32 forward 6144 x 16384 159,
-// 164; 12288^2 235, 242; 16384^2 391, 405; 16-bit forward 14336^2 179, 186; 16384^2
-// 217, 221; inverse 162, 169 and 203, 207; 9/7 16-bit forward 14336^2 188, 191;
-// 15624 x 16384 297, 306 (12288 x 16384 182, 179). The others never gain: 5/3 FP32
+// Of 5/3 launches and 16-bit 9/7 forwards, short segments keep the rows in flight
+// together where the grid evens out by itself: from 10 workgroups per CU on (9/7:
+// 12), us with those and with the segment weighed best: 5/3 FP32 forward 8192 x
+// 10240 127, 136; 12288^2 235, 242; 16384^2 391, 405 (8192^2 113, 109); 16-bit
+// forward 9240 x 16384 162, 174; 16384^2 217, 221; inverse 133, 140 and 203, 207
+// (12288^2 125, 122); 9/7 16-bit forward 14336^2 188, 191; 15624 x 16384 297, 306
+// (12288^2 138, 135; 12288 x 16384 182, 179). The others never gain: 5/3 FP32
 // inverse 16384^2 401, 392; 9/7 16384^2 FP32 forward 411, 405, inverse 408, 381;
 // 16-bit inverse 219, 215; 12288 x 16384 173, 166. Launches of several images, whose
 // heights differ, take the short ones from 8 per CU on.
@@ -358,8 +359,9 @@ int head_segment(const HeadShape *im, int n, int wavelet, bool wide, bool invers
     const double kPairTimeStream2 = 1.7;
     const int64_t cus = device_cus();
     const int many = !wide ? 18 : inverse ? 15 : 9;
-    const bool evens = wavelet == DWT2_CDF53 ? !(wide && inverse) : !wide && !inverse;
-    const int even = n > 1 ? 8 : evens ? 12 : 0;
+    const int even = n > 1 ? 8
+                     : wavelet == DWT2_CDF53 ? (wide && inverse ? 0 : 10)
+                                             : (wide || inverse ? 0 : 12);
     if (even && head_tasks(im, n, many) >= even * kHeadWaves * cus) return many;
     const int halo = wavelet == DWT2_CDF97 ? 6 : 4, D = kHeadDepth;
     int tallest = 1;
